@@ -51,7 +51,8 @@ HBM_PEAK_GBS = 8000.0
 FP64_PEAK_TFLOPS = 78.6
 FP32_PEAK_TFLOPS = 157.3
 METRIC = "DOF-updates/s per RK stage"
-KERNEL_SRC = os.path.join(ROOT, "paper_1506_06140_amd", "csrc", "dg_kernels.hip")
+CSRC = os.path.join(ROOT, "paper_1506_06140_amd", "csrc")
+KERNEL_SRC = ("dg_device.h", "dg_line.h", "dg_march3d.hip", "dg_kernels.hip")
 PROFILES = os.path.join(ROOT, "profiles")
 
 # source regions whose text fingerprints a kernel (a counter summary taken on
@@ -61,12 +62,12 @@ _HELPERS = [
     ("// Reciprocal and reciprocal square root from the hardware estimates plus",
      "// HLLC numerical flux in +a between traces UL (low side) and UR (high side),"),
     ("// HLLC numerical flux in +a between traces UL (low side) and UR (high side),",
-     "// ---------------------------------------------------------------------------\n// Right-hand side and fused stage."),
+     "// One stage of the time integrator in Shu-Osher form (App. D): with u the"),
 ]
 KERNELS = {
-    "stage3d": dict(name="k_rhs_mfma3d<2>", traffic="k_rhs_mfma3d_kh3d128_k2_traffic.txt",
-                    regions=_HELPERS + [("// 3D right-hand side + stage with the contractions on MFMA (FP64; FP32 and",
-                                         "// Discrete adjoint of the right-hand side and of the SSP-RK3 stages.")]),
+    "stage3d": dict(name="k_rhs_march3d<2>", traffic="k_rhs_march3d_kh3d128_k2_traffic.txt",
+                    regions=[("// One-dimensional building blocks of the sum-factorised stage kernels: the",
+                              "// Planes per wave: all waves run alike, one (k = 2) or two (k = 1) per SIMD at")]),
     "stage3d_amr": dict(name="k_rhs_mfma3d<3,AMR>", traffic="k_rhs_mfma3d_blast64box_k3_traffic.txt",
                         regions=_HELPERS + [("// 3D right-hand side + stage with the contractions on MFMA (FP64; FP32 and",
                                              "// Discrete adjoint of the right-hand side and of the SSP-RK3 stages.")]),
@@ -99,13 +100,13 @@ def alg_work(d: int, k: int):
 def kernel_hash(kernel: str) -> str:
     """Fingerprint of the source of a benchmarked kernel (its own region plus
     the Riemann solver and the reciprocal helpers)."""
-    src = open(KERNEL_SRC).read()
+    src = "".join(open(os.path.join(CSRC, f)).read() for f in KERNEL_SRC)
     parts = []
     for a, b in KERNELS[kernel]["regions"]:
         i = src.find(a)
         j = src.find(b, i + 1) if i >= 0 else -1
         if i < 0 or j < 0:
-            raise RuntimeError(f"kernel fingerprint marker not found in {KERNEL_SRC}: {a if i < 0 else b!r}")
+            raise RuntimeError(f"kernel fingerprint marker not found in {CSRC}: {a if i < 0 else b!r}")
         parts.append(src[i:j])
     return hashlib.sha256("".join(parts).encode()).hexdigest()[:16]
 
@@ -387,7 +388,7 @@ def variants():
     # fused RHS + stage launch, HIP events), with the limiter pass
     kinds = {
         "kh3d": ("3D shear layer 128^3, k=2", {},
-                 {"fp64_mfma": "k_rhs_mfma3d<2>", "fp64_valu": "k_rhs_stage<3,2,double>",
+                 {"fp64_mfma": "k_rhs_march3d<2>", "fp64_valu": "k_rhs_stage<3,2,double>",
                   "fp32_valu": "k_rhs_stage<3,2,float>", "fp32_mfma": None,
                   "bf16_mfma": "k_rhs_mfma3d<2,float,BF16 volume>"}),
         "blast_amr": ("3D blast, 64^3 base grid + refined 32^3 box (64^3 fine cells), k=3", {"eps": 1e-4},

@@ -104,14 +104,17 @@ typedef struct {
                       /* DG_TILE2D_AUTO (0, the rule of dg_init),              */
                       /* DG_TILE2D_8X8 or DG_TILE2D_LARGE (16 x 16 for k <= 2, */
                       /* 16 x 8 for k = 3, 4); results equal to rounding       */
-  int path3d;         /* 3D, k = 2 or 3, no gravity: DG_PATH3D_AUTO (0) runs   */
-                      /* the stage kernel's contractions on MFMA: FP64 on     */
-                      /* FP64 MFMA; FP32 on FP32 MFMA at k = 3 and on refined */
-                      /* boxes (FP32 at k = 2 on a uniform grid keeps the     */
-                      /* one-thread-per-cell kernel, faster there);           */
-                      /* DG_PATH3D_VALU runs them on the vector ALU (one      */
-                      /* thread per cell; FP64 at k = 3 four lanes per cell); */
-                      /* results equal to rounding                            */
+  int path3d;         /* 3D, no gravity: DG_PATH3D_AUTO (0) runs FP64 on       */
+                      /* uniform grids at k = 1 and 2 on the sum-factorised    */
+                      /* kernel (k = 2 on grids of up to 16384 cells and       */
+                      /* states of 4 GB or more excepted), and otherwise at    */
+                      /* k = 2 or 3 the stage kernel's contractions on MFMA:   */
+                      /* FP64 on FP64 MFMA; FP32 on FP32 MFMA at k = 3 and on  */
+                      /* refined boxes (FP32 at k = 2 on a uniform grid keeps  */
+                      /* the one-thread-per-cell kernel, faster there);        */
+                      /* DG_PATH3D_VALU runs them on the vector ALU (one       */
+                      /* thread per cell; FP64 at k = 3 four lanes per cell);  */
+                      /* results equal to rounding                             */
 } dg_config;
 
 /* Builds the basis and quadrature tables (Gauss-Legendre nodes by Newton

@@ -1,0 +1,11 @@
+// Choice between the sum-factorised stage kernels and the others.
+#include "dg_device.h"
+
+bool dg::launch_line(const dg_ctx *c, const double *w, double *out, const double *dt, int mode, const Mix &mx,
+                     const RateOp &ro, hipStream_t s, int *err) {
+  if (ro.op == RATE_NONE && march3d_takes(c)) {
+    *err = launch_march3d(c, w, out, dt, mode, mx, s);
+    return true;
+  }
+  return false;
+}
