@@ -100,10 +100,10 @@ typedef struct {
   int refine_hi[3];   /* axis are covered by 2(hi-lo) fine cells per axis of   */
                       /* half the edge (Sec. 4); lo == hi (e.g. all zero) for  */
                       /* a uniform grid.  Requires 1 <= lo < hi <= n-1.        */
-  int tile2d;         /* 2D uniform grids: cell tile of the stage kernel,      */
-                      /* DG_TILE2D_AUTO (0, the rule of dg_init),              */
-                      /* DG_TILE2D_8X8 or DG_TILE2D_LARGE (16 x 16 for k <= 2, */
-                      /* 16 x 8 for k = 3, 4); results equal to rounding       */
+  int tile2d;         /* 2D uniform grids: the stage kernel.  DG_TILE2D_AUTO   */
+                      /* (0): the rule of dg_init; DG_TILE2D_8X8 or            */
+                      /* DG_TILE2D_LARGE (16 x 16 for k <= 2, 16 x 8 for k =   */
+                      /* 3, 4): tiles of that shape; results equal to rounding */
   int path3d;         /* 3D, no gravity: DG_PATH3D_AUTO (0) runs FP64 on       */
                       /* uniform grids at k = 1 and 2 on the sum-factorised    */
                       /* kernel (k = 2 on grids of up to 16384 cells and       */
@@ -122,10 +122,11 @@ typedef struct {
  * for k <= 3, the refinement matrices of Sec. 4.2 (eq. ref_pa_integral),
  * copies them to the current device and allocates scratch.  Host-to-device
  * copies happen here only.  *out receives the context.  With
- * cfg->tile2d = DG_TILE2D_AUTO, on 2D grids without refinement the stage
- * kernel works on tiles of 8 x 8 cells for k <= 3; at k = 4 on tiles of
- * 16 x 8 cells, or of 8 x 8 when the grid has fewer 16 x 8 tiles than the GPU
- * has compute units.  DG_EUNSUPPORTED for a base grid or a fine block of more
+ * cfg->tile2d = DG_TILE2D_AUTO, on 2D grids without refinement the FP64
+ * stage kernel splits a cell's work over four waves (states below 4 GB; with
+ * gravity k <= 3); elsewhere it works on tiles of 8 x 8 cells for k <= 3 and at
+ * k = 4 on tiles of 16 x 8 cells, or of 8 x 8 when the grid has fewer 16 x 8
+ * tiles than the GPU has compute units.  DG_EUNSUPPORTED for a base grid or a fine block of more
  * than 2^31 cells (kernels index a block's cells in 32 bits). */
 int dg_init(const dg_config *cfg, dg_ctx **out);
 

@@ -620,6 +620,9 @@ __device__ inline void static_for(F &&f) {
 // else it returns false.
 bool launch_line(const dg_ctx *c, const double *w, double *out, const double *dt, int mode, const Mix &mx,
                  const RateOp &ro, hipStream_t s, int *err);
+bool split2d_takes(const dg_ctx *c);
+int launch_split2d(const dg_ctx *c, const double *w, double *out, const double *dt, int mode, const Mix &mx,
+                   const RateOp &ro, hipStream_t s);
 bool march3d_takes(const dg_ctx *c);
 int launch_march3d(const dg_ctx *c, const double *w, double *out, const double *dt, int mode, const Mix &mx,
                    hipStream_t s);

@@ -1,0 +1,68 @@
+// What the sum-factorised stage kernels (dg_split2d.hip, dg_march3d.hip) share.
+#pragma once
+
+#include "dg_line.h"
+
+// Keeps the scheduler from interleaving across it: each phase's temporaries
+// die before the next phase's are formed.
+#define DG_FENCE __builtin_amdgcn_sched_barrier(0)
+
+namespace dg {
+
+// A state as a buffer: byte offsets of 32 bits (the launcher checks that the
+// state is below 4 GB), the (variable, mode) plane as the scalar offset, so a
+// load takes one vector register of address and no scalar base of its own.
+struct StateBuf {
+  __amdgpu_buffer_rsrc_t r;
+  unsigned plane;  // bytes of one (variable, mode) plane
+  __device__ __forceinline__ StateBuf(const double *p, long nc, int planes)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<double *>(p), 0, (int)(unsigned)(nc * 8 * planes), 0x00027000)),
+        plane((unsigned)nc * 8u) {}
+  template <int AUX = 0>
+  __device__ __forceinline__ double load(unsigned cell8, unsigned off) const {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const u2 x = __builtin_amdgcn_raw_buffer_load_b64(r, cell8, off, AUX);
+    return __hiloint2double((int)x.y, (int)x.x);
+  }
+  template <int AUX = 0>
+  __device__ __forceinline__ void store(double v, unsigned cell8, unsigned off) const {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const u2 x = {(unsigned)__double2loint(v), (unsigned)__double2hiint(v)};
+    __builtin_amdgcn_raw_buffer_store_b64(x, r, cell8, off, AUX);
+  }
+};
+constexpr int NT = 2;  // non-temporal: data this launch touches once
+
+// the N weights of V variables of one cell, raw (off: byte offset of the first plane)
+template <int V, int N, int AUX = 0>
+__device__ __forceinline__ void load_cell(const StateBuf &w, unsigned cell8, double (&r)[V][N], unsigned off = 0) {
+#pragma unroll
+  for (int v = 0; v < V; ++v)
+#pragma unroll
+    for (int l = 0; l < N; ++l) {
+      r[v][l] = w.load<AUX>(cell8, off);
+      off += w.plane;
+    }
+}
+
+// Planes per wave: all waves run alike, one (k = 2) or two (k = 1) per SIMD at
+// a time, and a wave's cost is about its planes plus a quarter (the first
+// face, the first loads).  128^3, k = 2, us per launch for 4, 7, 8, 12, 16, 32
+// planes: 1366, 1346, 1423, 1330, 1647, 2164; k = 1: 448, 444, 453, 448, 500,
+// 609; 64^3, k = 1, for 1, 3, 6, 12 planes: 87, 79, 85, 150.
+inline int march_len(long columns, int nz, long slots) {
+  double best = 0.0;
+  int at = 1;
+  for (int len = 1; len <= nz && len <= 64; ++len) {
+    const long waves = (columns * ((nz + len - 1) / len) + 61) / 62;
+    const double cost = (double)((waves + slots - 1) / slots) * (len + 0.25);
+    if (len == 1 || cost < best) {
+      best = cost;
+      at = len;
+    }
+  }
+  return at;
+}
+
+
+}  // namespace dg

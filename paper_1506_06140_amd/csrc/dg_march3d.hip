@@ -1,37 +1,7 @@
 // 3D right-hand side + stage, one thread per cell, sum-factorised (FP64).
-#include <algorithm>
-
-#include "dg_line.h"
-
-// Keeps the scheduler from interleaving across it: each phase's temporaries
-// die before the next phase's are formed.
-#define DG_FENCE __builtin_amdgcn_sched_barrier(0)
+#include "dg_march.h"
 
 namespace dg {
-
-// A state as a buffer: byte offsets of 32 bits (the launcher checks that the
-// state is below 4 GB), the (variable, mode) plane as the scalar offset, so a
-// load takes one vector register of address and no scalar base of its own.
-struct StateBuf {
-  __amdgpu_buffer_rsrc_t r;
-  unsigned plane;  // bytes of one (variable, mode) plane
-  __device__ __forceinline__ StateBuf(const double *p, long nc, int planes)
-      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<double *>(p), 0, (int)(unsigned)(nc * 8 * planes), 0x00027000)),
-        plane((unsigned)nc * 8u) {}
-  template <int AUX = 0>
-  __device__ __forceinline__ double load(unsigned cell8, unsigned off) const {
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    const u2 x = __builtin_amdgcn_raw_buffer_load_b64(r, cell8, off, AUX);
-    return __hiloint2double((int)x.y, (int)x.x);
-  }
-  template <int AUX = 0>
-  __device__ __forceinline__ void store(double v, unsigned cell8, unsigned off) const {
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    const u2 x = {(unsigned)__double2loint(v), (unsigned)__double2hiint(v)};
-    __builtin_amdgcn_raw_buffer_store_b64(x, r, cell8, off, AUX);
-  }
-};
-constexpr int NT = 2;  // non-temporal: data this launch touches once
 
 struct MarchGrid {
   int nx, ny, nz;
@@ -257,19 +227,6 @@ __device__ __forceinline__ void volume_term(W &&w, double gm1, const double (&m)
   }
 }
 
-// the N weights of the five variables of one cell, raw
-template <int N, int AUX = 0>
-__device__ __forceinline__ void load_cell(const StateBuf &w, unsigned cell8, double (&r)[5][N]) {
-  unsigned off = 0;
-#pragma unroll
-  for (int v = 0; v < 5; ++v)
-#pragma unroll
-    for (int l = 0; l < N; ++l) {
-      r[v][l] = w.load<AUX>(cell8, off);
-      off += w.plane;
-    }
-}
-
 // 3D right-hand side and stage, one thread per cell.
 //
 // FP64 matrix and vector instructions share one datapath, so what counts is
@@ -342,7 +299,7 @@ __global__ __launch_bounds__(64, 1) void k_rhs_march3d(const double *__restrict_
   };
 
   double wc[5][N];  // this lane's own cell
-  load_cell<N>(ws, plane(z0 - 1) + col, wc);
+  load_cell<5, N>(ws, plane(z0 - 1) + col, wc);
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
     double t[N2];
@@ -350,7 +307,7 @@ __global__ __launch_bounds__(64, 1) void k_rhs_march3d(const double *__restrict_
 #pragma unroll
     for (int j = 0; j < N2; ++j) low(v, j) = t[j];
   }
-  load_cell<N>(ws, plane(z0) + col, wc);
+  load_cell<5, N>(ws, plane(z0) + col, wc);
 #pragma unroll 1
   for (int s = 0; s <= g.len; ++s) {
     const int zr = z0 + s;  // the cell above the face
@@ -373,7 +330,7 @@ __global__ __launch_bounds__(64, 1) void k_rhs_march3d(const double *__restrict_
     const bool st = own && s > 0 && zr - 1 < g.nz;
     const unsigned cb = (unsigned)min(max(zr - 1, 0), g.nz - 1) * nxy8 + col;
     double y0[5][N];
-    load_cell<N, NT>(ys, cb, y0);  // in flight during the face
+    load_cell<5, N, NT>(ys, cb, y0);  // in flight during the face
     DG_FENCE;
     face_flux<K, 2, FX>(low, ch, g.gamma, m);
     if (s > 0) {  // the cell below is complete: its last face and its stage update
@@ -416,7 +373,7 @@ __global__ __launch_bounds__(64, 1) void k_rhs_march3d(const double *__restrict_
       DG_FENCE;
     }
     double nb[5][N];
-    load_cell<N>(ws, cell + dyl, nb);  // in flight during the face
+    load_cell<5, N>(ws, cell + dyl, nb);  // in flight during the face
     DG_FENCE;
     face_flux<K, 0, FX>(low, ch, g.gamma, m);
 #pragma unroll
@@ -445,7 +402,7 @@ __global__ __launch_bounds__(64, 1) void k_rhs_march3d(const double *__restrict_
         }
         DG_FENCE;
       }
-      load_cell<N>(ws, next, nb);
+      load_cell<5, N>(ws, next, nb);
       DG_FENCE;
       face_flux<K, 1, FX>(low, ch, g.gamma, m);
 #pragma unroll
@@ -484,29 +441,6 @@ __global__ __launch_bounds__(64, 1) void k_rhs_march3d(const double *__restrict_
 }
 
 }  // namespace dg
-
-namespace {
-
-// Planes per wave: all waves run alike, one (k = 2) or two (k = 1) per SIMD at
-// a time, and a wave's cost is about its planes plus a quarter (the first
-// face, the first loads).  128^3, k = 2, us per launch for 4, 7, 8, 12, 16, 32
-// planes: 1366, 1346, 1423, 1330, 1647, 2164; k = 1: 448, 444, 453, 448, 500,
-// 609; 64^3, k = 1, for 1, 3, 6, 12 planes: 87, 79, 85, 150.
-int march_len(long columns, int nz, long slots) {
-  double best = 0.0;
-  int at = 1;
-  for (int len = 1; len <= nz && len <= 64; ++len) {
-    const long waves = (columns * ((nz + len - 1) / len) + 61) / 62;
-    const double cost = (double)((waves + slots - 1) / slots) * (len + 0.25);
-    if (len == 1 || cost < best) {
-      best = cost;
-      at = len;
-    }
-  }
-  return at;
-}
-
-}  // namespace
 
 // FP64 on uniform 3D grids at k = 1 and 2 without gravity, states below 4 GB
 // (32-bit byte offsets).  At k = 2 a grid of at most one 64-cell block per

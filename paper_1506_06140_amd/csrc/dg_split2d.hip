@@ -1,0 +1,432 @@
+// 2D right-hand side + stage, a cell's work split over four waves (FP64).
+#include "dg_march.h"
+
+namespace dg {
+
+// Coefficients (by tangential exponent) of the trace of w on the face normal
+// to A at xi_A = -1 (S = 0) or +1.
+template <int K, int A, int S>
+__device__ __forceinline__ void edge_coefs(const double (&w)[(K + 1) * (K + 2) / 2], double (&c)[K + 1]) {
+#pragma clang fp contract(off)
+  constexpr Line<K> L{};
+  static_for<0, K + 1>([&](auto T_) {
+    constexpr int t = decltype(T_)::value;
+    double x = w[A == 0 ? mode_index<2>(0, t, 0) : mode_index<2>(t, 0, 0)];
+    static_for<1, K + 1 - t>([&](auto N_) {
+      constexpr int n = decltype(N_)::value;
+      constexpr double s = (S == 0 && n % 2 ? -1.0 : 1.0) * L.b[n];
+      x = fma(w[A == 0 ? mode_index<2>(n, t, 0) : mode_index<2>(t, n, 0)], s, x);
+    });
+    c[t] = x;
+  });
+}
+
+// moments m[v][e] of the HLLC flux over the K + 1 face points
+template <int K, int A, int FX>
+__device__ __forceinline__ void edge_flux(const double (&cl)[4][K + 1], const double (&ch)[4][K + 1], double gamma,
+                                          double (&m)[4][K + 1]) {
+  constexpr int n1 = K + 1;
+  double ul[4][n1], uh[4][n1];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    line_values<K, K>(cl[v], ul[v]);
+    line_values<K, K>(ch[v], uh[v]);
+  }
+  DG_FENCE;
+  double F[4][n1];
+#pragma unroll
+  for (int i = 0; i < n1; ++i) {
+    const double UL[4] = {ul[0][i], ul[1][i], ul[2][i], ul[3][i]}, UR[4] = {uh[0][i], uh[1][i], uh[2][i], uh[3][i]};
+    double f[4];
+    hllc_line<2, A, FX>(UL, UR, gamma, f);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) F[v][i] = f[v];
+    if (i % 2 == 1) DG_FENCE;
+  }
+  DG_FENCE;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) line_moments<K, K>(F[v], m[v]);
+}
+
+// the outward flux of side S (moments m) taken off the accumulators
+template <int K, int A, int S>
+__device__ __forceinline__ void edge_lift(const double (&m)[K + 1], double (&acc)[(K + 1) * (K + 2) / 2]) {
+  constexpr Line<K> L{};
+  static_for<0, (K + 1) * (K + 2) / 2>([&](auto L_) {
+    constexpr int l = decltype(L_)::value, ex = mode_exp<2>(l, 0), ey = mode_exp<2>(l, 1);
+    constexpr int n = A == 0 ? ex : ey, t = A == 0 ? ey : ex;
+    constexpr double s = (S == 0 ? (n % 2 ? -1.0 : 1.0) : -1.0) * L.b[n];
+    acc[l] = fma(m[t], s, acc[l]);
+  });
+}
+
+// Volume integral of one cell (see volume_term in dg_march3d.hip), with the
+// gravity source (GRAV: its values at the nodes, (dx/2) w_q included, through
+// gv(axis, node)), variable by variable through set(v, row).
+template <int K, bool GRAV, class W, class G2, class Set>
+__device__ __forceinline__ void area_term(W &&w, double gm1, G2 &&gv, Set &&set) {
+  constexpr int n1 = K + 1, N = (K + 1) * (K + 2) / 2, NM = K * (K + 1) / 2;
+  constexpr Line<K> L{};
+  const Line<K> &T = line_const<K>();
+  double M[5][NM];  // xx xy yy, hx hy
+  double src[3][GRAV ? N : 1];  // the source's projection (momenta, energy)
+  if constexpr (GRAV)
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int l = 0; l < N; ++l) src[t][l] = 0.0;
+#pragma unroll
+  for (int t = 0; t < 5; ++t)
+#pragma unroll
+    for (int j = 0; j < NM; ++j) M[t][j] = 0.0;
+#pragma unroll 1
+  for (int iy = 0; iy < n1; ++iy) {
+    asm volatile("" ::: "memory");  // weights in LDS are read row by row, not held in registers
+    double p[n1];
+#pragma unroll
+    for (int e = 0; e < n1; ++e) p[e] = T.p[iy][e];
+    const double wy = T.w[iy];
+    double U[4][n1];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      double c1[n1];
+      static_for<0, n1>([&](auto E_) {
+        constexpr int ex = decltype(E_)::value;
+        double t = w(v, mode_index<2>(ex, 0, 0));
+        static_for<1, n1 - ex>([&](auto Y_) {
+          constexpr int ey = decltype(Y_)::value;
+          t = fma(w(v, mode_index<2>(ex, ey, 0)), p[ey], t);
+        });
+        c1[ex] = t;
+      });
+      line_values<K, K>(c1, U[v]);
+    }
+    double G[5][n1], S[3][n1];
+#pragma unroll
+    for (int i = 0; i < n1; ++i) {
+      const double ir = rcp3(U[0][i]);
+      const double vx = U[1][i] * ir, vy = U[2][i] * ir;
+      const double ke = fma(U[1][i], vx, U[2][i] * vy);
+      const double pr = gm1 * fma(-0.5, ke, U[3][i]), H = U[3][i] + pr;
+      G[0][i] = fma(U[1][i], vx, pr);
+      G[1][i] = U[1][i] * vy;
+      G[2][i] = fma(U[2][i], vy, pr);
+      G[3][i] = H * vx;
+      G[4][i] = H * vy;
+      if constexpr (GRAV) {  // the values carry (dx/2) w_q
+        const double gx = gv(0, iy * n1 + i), gy = gv(1, iy * n1 + i);
+        S[0][i] = U[0][i] * gx;
+        S[1][i] = U[0][i] * gy;
+        S[2][i] = fma(U[1][i], gx, U[2][i] * gy);
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < 5; ++t) {
+      double s[K];
+      line_moments<K, K - 1>(G[t], s);
+      static_for<0, NM>([&](auto J_) {
+        constexpr int j = decltype(J_)::value, ex = mode_exp<2>(j, 0), ey = mode_exp<2>(j, 1);
+        M[t][j] = fma(s[ex], wy * p[ey], M[t][j]);
+      });
+    }
+    if constexpr (GRAV) {
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+        static_for<0, n1>([&](auto E_) {
+          constexpr int ex = decltype(E_)::value;
+          double s = S[t][0] * L.p[0][ex];
+#pragma unroll
+          for (int i = 1; i < n1; ++i) s = fma(S[t][i], L.p[i][ex], s);
+          static_for<0, n1 - ex>([&](auto Y_) {
+            constexpr int ey = decltype(Y_)::value, l = mode_index<2>(ex, ey, 0);
+            src[t][l] = fma(s, p[ey], src[t][l]);
+          });
+        });
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    double acc[N];
+#pragma unroll
+    for (int l = 0; l < N; ++l) acc[l] = GRAV && v > 0 ? src[v - 1][l] : 0.0;
+    static_for<1, N>([&](auto L_) {
+      constexpr int l = decltype(L_)::value, ex = mode_exp<2>(l, 0), ey = mode_exp<2>(l, 1);
+      static_for<0, 2>([&](auto A_) {
+        constexpr int a = decltype(A_)::value, ea = a == 0 ? ex : ey;
+        static_for<0, ea>([&](auto J_) {
+          constexpr int j = decltype(J_)::value;
+          if constexpr ((ea - j) % 2 == 1) {
+            constexpr int q = a == 0 ? mode_index<2>(j, ey, 0) : mode_index<2>(ex, j, 0);
+            constexpr double dc = L.dc[ea][j];
+            const int t = v == 1 ? a : v == 2 ? 1 + a : 3 + a;
+            acc[l] = v == 0 ? fma(w(1 + a, q), 4.0 * dc, acc[l]) : fma(M[t][q], dc, acc[l]);
+          }
+        });
+      });
+    });
+    set(v, acc);
+  }
+}
+
+struct SplitGrid {
+  int nx, ny;
+  long nc;
+  int wall[2];
+  double fac, gamma;
+  long columns;  // (nx + 1) ny
+};
+
+// 2D right-hand side and stage.
+//
+// A block of four waves takes 64 consecutive positions of rows extended by one
+// (position nx of a row is only the face behind its last cell; the last lane
+// is the next block's first).  Wave 0 forms the cells' volume terms, waves 1,
+// 2 and 3 the fluxes of their x low, y low and y high faces; the high x face
+// is the next lane's low one.  After one barrier wave v lifts the four faces'
+// moments of variable v onto its volume term and applies the stage update.
+// Each phase is a contraction of one axis at a time in one lane (no
+// reduction over lanes, no table reads), the four phases cost about the same
+// (k = 2: 440 issue slots the volume, 520 a face), and a y face is solved by
+// both of its cells with the same code and inputs: the same flux bit for bit.
+// A small grid is bound by the length of one wave's work, which the split cuts
+// to a third of a cell's; a large one by the vector ALU (43 % at 512^2, k = 2)
+// and its loads' latency, with the memory floor at half its time.
+// Against the 8x8 tiles of four lanes per cell, us per launch: k = 1 32^2 5.6
+// -> 4.0, 256^2 10.0 -> 8.5; k = 2 32^2 7.8 -> 5.2, 256^2 17.9 -> 14.3, 512^2 64
+// -> 40.5; k = 3 32^2 11.6 -> 7.1, 512^2 127 -> 76; k = 4 32^2 33.6 -> 11.7, 256^2
+// 77.5 -> 39.7.  One thread per cell marching along y (no second solve of a y
+// face) took 9.4, 19.5 and 46 us at k = 2.  Loading the own cell once per block
+// and sharing its traces through LDS halved the loads and changed nothing.
+// Registers bound the waves per SIMD below: one step lower spills, and 30
+// spilled registers cost 60 % (k = 3, 512^2: 76 -> 124 us).
+template <int K, int FX, bool PER, bool GRAV>
+__global__ __launch_bounds__(256, GRAV ? (K == 1 ? 4 : K == 2 ? 2 : 1) : K == 1 ? 5 : K == 2 ? 4 : K == 3 ? 3 : 2) void k_rhs_split2d(
+    const double *__restrict__ w, double *__restrict__ out, const double *__restrict__ dtp, SplitGrid g, int mode, Mix mx,
+    int *__restrict__ flag, RateOp ro, const double *__restrict__ grav) {
+  constexpr int N = (K + 1) * (K + 2) / 2, n1 = K + 1;
+  __shared__ double sv[4 * N * 64];       // volume term [v][l][lane]
+  __shared__ double sm[3 * 4 * n1 * 64];  // face moments [face: x low, y low, y high][v][e][lane]
+  __shared__ double mean[4 * 64];
+  const int lane = threadIdx.x & 63, role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nb = gridDim.x, xcd = blockIdx.x % 8, jb = blockIdx.x / 8;
+  const long blk = (long)xcd * (nb / 8) + min(xcd, nb % 8) + jb;
+  const long e0 = 63 * blk + lane;
+  const long e = min(e0, g.columns - 1);
+  const int px = (int)((unsigned)e % (unsigned)(g.nx + 1)), iy = (int)((unsigned)e / (unsigned)(g.nx + 1));
+  const bool own = px < g.nx && lane < 63 && e0 < g.columns;
+  const StateBuf ws(w, g.nc, 4 * N), os(out, g.nc, 4 * N);
+  const unsigned nx8 = 8u * (unsigned)g.nx, row = (unsigned)iy * nx8;
+  const unsigned cell = row + 8u * (unsigned)(px < g.nx ? px : 0);
+  double dt = 0.0;
+  if (mode != 0) {
+    if (ro.op == RATE_DT) {
+      double r = 0.0;
+#pragma unroll
+      for (int k = 0; k < RATE_SLOTS; ++k)
+        r = fmax(r, __longlong_as_double((long long)*rate_slot(ro.word, k)));
+      dt = ro.cfl_fk / r;
+      if (blockIdx.x == 0 && threadIdx.x == 0) ro.dt_out[0] = dt;
+    } else {
+      dt = *dtp;
+    }
+  }
+  if (blockIdx.x == 0 && ro.op == RATE_CLEAR && threadIdx.x < RATE_SLOTS) ro.word[RATE_STRIDE * threadIdx.x] = 0ull;
+
+  if (role == 0) {
+    double wc[4][N];
+    load_cell<4, N>(ws, cell, wc);
+    // at k >= 3 the weights wait in LDS (the term's own place: its rows of the
+    // momenta are read before they are replaced)
+    if constexpr (K >= 3)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int l = 0; l < N; ++l) sv[(v * N + l) * 64 + lane] = wc[v][l];
+    area_term<K, GRAV>(
+        [&](int v, int l) __attribute__((always_inline)) {
+          if constexpr (K >= 3) return sv[(v * N + l) * 64 + lane];
+          else return wc[v][l];
+        },
+        g.gamma - 1.0,
+        [&](int a, int q) __attribute__((always_inline)) {
+          return GRAV ? grav[(long)(a * n1 * n1 + q) * g.nc + (cell >> 3)] : 0.0;
+        },
+        [&](int v, const double(&row)[N]) __attribute__((always_inline)) {
+#pragma unroll
+          for (int l = GRAV ? 0 : 1; l < N; ++l) sv[(v * N + l) * 64 + lane] = row[l];
+        });
+  } else {
+    // the face's two cells; a ghost (transmissive wall) takes the other's trace
+    unsigned lo = cell, hi = cell;
+    bool gl = false, gh = false;
+    if (role == 1) {
+      lo = row + 8u * (unsigned)(px > 0 ? px - 1 : g.nx - 1);
+      if constexpr (!PER) {
+        gl = g.wall[0] && px == 0;
+        gh = g.wall[0] && px == g.nx;
+      }
+    } else if (role == 2) {
+      lo = iy > 0 ? cell - nx8 : cell + (unsigned)(g.ny - 1) * nx8;
+      if constexpr (!PER) gl = g.wall[1] && iy == 0;
+    } else {
+      hi = iy < g.ny - 1 ? cell + nx8 : cell - (unsigned)(g.ny - 1) * nx8;
+      if constexpr (!PER) gh = g.wall[1] && iy == g.ny - 1;
+    }
+    double cl[4][n1], ch[4][n1], m[4][n1];
+    auto face = [&](auto A_) __attribute__((always_inline)) {
+      constexpr int A = decltype(A_)::value;
+      // two variables' weights at a time at k >= 3: all eight rows at once
+      // would be the kernel's register peak
+#pragma unroll
+      for (int v0 = 0; v0 < 4; v0 += (K >= 3 ? 2 : 4)) {
+        constexpr int NVL = K >= 3 ? 2 : 4;
+        double a[NVL][N], b[NVL][N];
+        const unsigned off = (unsigned)(v0 * N) * ws.plane;
+        load_cell<NVL, N>(ws, lo, a, off);
+        load_cell<NVL, N>(ws, hi, b, off);
+#pragma unroll
+        for (int i = 0; i < NVL; ++i) {
+          const int v = v0 + i;
+          edge_coefs<K, A, 1>(a[i], cl[v]);
+          edge_coefs<K, A, 0>(b[i], ch[v]);
+          if constexpr (!PER)
+#pragma unroll
+            for (int j = 0; j < n1; ++j) {
+              const double x = cl[v][j], y = ch[v][j];
+              cl[v][j] = gl ? y : x;
+              ch[v][j] = gh ? x : y;
+            }
+        }
+        if constexpr (K >= 3) DG_FENCE;
+      }
+      edge_flux<K, A, FX>(cl, ch, g.gamma, m);
+    };
+    if (role == 1) face(std::integral_constant<int, 0>{});
+    else face(std::integral_constant<int, 1>{});
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int j = 0; j < n1; ++j) sm[(((role - 1) * 4 + v) * n1 + j) * 64 + lane] = m[v][j];
+  }
+  // the operands of this wave's share of the update (variable `role`), in
+  // flight across the barrier
+  double wo[N], y0[N];
+  const StateBuf ys(mode != 0 && mx.n > 0 ? mx.y[0] : w, g.nc, 4 * N);
+#pragma unroll
+  for (int l = 0; l < N; ++l) {
+    wo[l] = ws.load(cell, (unsigned)(role * N + l) * ws.plane);
+    y0[l] = ys.load(cell, (unsigned)(role * N + l) * ws.plane);
+  }
+  __syncthreads();
+
+  // variable `role`: the four faces lifted onto the volume term, the update
+  double acc[N];
+  acc[0] = GRAV ? sv[role * N * 64 + lane] : 0.0;
+#pragma unroll
+  for (int l = 1; l < N; ++l) acc[l] = sv[(role * N + l) * 64 + lane];
+  auto moments = [&](int f, int at, double (&m)[n1]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < n1; ++j) m[j] = sm[((f * 4 + role) * n1 + j) * 64 + at];
+  };
+  double m[n1];
+  moments(0, lane, m);
+  edge_lift<K, 0, 0>(m, acc);
+  moments(0, min(lane + 1, 63), m);
+  edge_lift<K, 0, 1>(m, acc);
+  moments(1, lane, m);
+  edge_lift<K, 1, 0>(m, acc);
+  moments(2, lane, m);
+  edge_lift<K, 1, 1>(m, acc);
+  bool bad = false;
+  const double cldt = mx.cl * dt;
+  if (own) {
+    unsigned off = (unsigned)(role * N) * os.plane;
+#pragma unroll
+    for (int l = 0; l < N; ++l) {
+      const double L = g.fac * acc[l];
+      bad |= L != L;
+      double o = L;
+      if (mode != 0) {
+        o = fma(cldt, L, mx.cu * wo[l]);
+        if (mx.n > 0) o = fma(mx.a[0], y0[l], o);
+        if (mx.n > 1) o = mix_tail(mx, o, (long)(role * N + l) * g.nc + (cell >> 3), 1);
+      }
+      os.store(o, cell, off);
+      off += os.plane;
+      if (l == 0) mean[role * 64 + lane] = o;
+    }
+  }
+  if (bad) atomicOr(flag, FLAG_NAN);
+  if (ro.op == RATE_FOLD) {
+    // signal rate of the new means (the limiters leave them unchanged): a wave
+    // max, one global max per block
+    __syncthreads();
+    if (role == 0) {
+      double r = 0.0;
+      if (own) {
+        const double U[4] = {mean[lane], mean[64 + lane], mean[128 + lane], mean[192 + lane]};
+        bool neg = false;
+        r = cell_rate<2>(U, g.gamma, ro.dx, neg, ro.gk, ro.gmax ? ro.gmax[cell >> 3] : 0.0);
+        if (neg) atomicOr(flag, FLAG_NEGATIVE);
+      }
+      r = wave_max(r);
+      if (lane == 0) atomicMax(rate_slot(ro.word, blockIdx.x), (unsigned long long)__double_as_longlong(r));
+    }
+  }
+}
+
+}  // namespace dg
+
+// FP64 on 2D grids without a refined box or a tree, unless the configuration
+// asks for a tile shape of the other kernel (tile2d) or has gravity at k = 4;
+// states below 4 GB (32-bit byte offsets).  Faster at every size measured,
+// 32^2 to 512^2.
+bool dg::split2d_takes(const dg_ctx *c) {
+  if (c->sh.d != 2 || c->amr || c->tree || c->cfg.precision != DG_FP64 || c->tile_small >= 0) return false;
+  if (c->gravity && c->sh.k > 3) return false;
+  return c->ncell * 8 * c->sh.nv * c->sh.N < (1LL << 32);
+}
+
+int dg::launch_split2d(const dg_ctx *c, const double *w, double *out, const double *dt, int mode, const Mix &mx,
+                       const RateOp &ro, hipStream_t s) {
+  SplitGrid g;
+  g.nx = (int)c->nx;
+  g.ny = (int)c->ny;
+  g.nc = c->ncell;
+  bool per = true;
+  for (int a = 0; a < 2; ++a) {
+    g.wall[a] = c->cfg.bc[a] == DG_BC_TRANSMISSIVE;
+    per = per && !g.wall[a];
+  }
+  g.fac = 2.0 / c->dx / 4.0;
+  g.gamma = c->cfg.gamma;
+  g.columns = (long)(g.nx + 1) * g.ny;
+  RateOp r = ro;
+  if (r.op == RATE_FOLD && c->gravity) {
+    r.gmax = c->gmax;
+    r.gk = c->grav_k;
+  }
+  const dim3 nb((unsigned)((g.columns + 62) / 63));
+  auto go = [&](auto K_, auto FX_) {
+    constexpr int K = decltype(K_)::value, FX = decltype(FX_)::value;
+    if (c->gravity) {
+      if constexpr (K <= 3)
+        hipLaunchKernelGGL((k_rhs_split2d<K, FX, false, true>), nb, dim3(256), 0, s, w, out, dt, g, mode, mx, c->flag, r, c->grav);
+    } else if (per) {
+      hipLaunchKernelGGL((k_rhs_split2d<K, FX, true, false>), nb, dim3(256), 0, s, w, out, dt, g, mode, mx, c->flag, r, nullptr);
+    } else {
+      hipLaunchKernelGGL((k_rhs_split2d<K, FX, false, false>), nb, dim3(256), 0, s, w, out, dt, g, mode, mx, c->flag, r, nullptr);
+    }
+  };
+  auto pick = [&](auto K_) {
+    if (c->cfg.flux == DG_HLLC_DAVIS) go(K_, std::integral_constant<int, DG_HLLC_DAVIS>{});
+    else go(K_, std::integral_constant<int, DG_HLLC_BATTEN>{});
+  };
+  switch (c->sh.k) {
+    case 1: pick(std::integral_constant<int, 1>{}); break;
+    case 2: pick(std::integral_constant<int, 2>{}); break;
+    case 3: pick(std::integral_constant<int, 3>{}); break;
+    default: pick(std::integral_constant<int, 4>{}); break;
+  }
+  return (int)hipGetLastError();
+}
