@@ -1609,12 +1609,19 @@ __device__ inline double tau_root(const double *Ub, const double *Uq, double gam
   return fmin(fmax(t, 0.0), 1.0);
 }
 
-// Smallest x over the 64 lanes of the wave (every lane active).
-__device__ inline double wave_min(double x) {
+// Smallest x over the G lanes of a group (lanes G i .. G i + G - 1, all active).
+template <int G>
+__device__ inline double group_min(double x) {
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) x = fmin(x, __shfl_xor(x, o));
+  for (int o = G / 2; o >= 1; o >>= 1) x = fmin(x, __shfl_xor(x, o));
   return x;
 }
+
+// Lanes that share a listed cell's points: the smallest power of two that
+// holds the NS points, so that a wave takes 64 / G cells at once (2D, k = 1: 8
+// points, 8 cells; one cell per wave left 56 lanes idle: 47 -> 6 us for the
+// 128^2 cold disc, whose whole disc is listed).
+constexpr int pos_lanes(int ns) { return ns <= 8 ? 8 : ns <= 16 ? 16 : ns <= 32 ? 32 : 64; }
 
 // Appends the cells of this wave with need set to the list plist (plist[0]
 // counts, plist[1 + i] holds the i-th cell id): one atomic per wave.  Every
@@ -1630,19 +1637,20 @@ __device__ inline void wave_append(bool need, int id, int *plist) {
 }
 
 // The point loop of the positivity pass (Sec. 3.4) for one cell, its
-// points shared by the 64 lanes of a wave (every lane calls with the same
-// cell): the cell's coefficient (v, l) is c[(v N + l) st]; h is its
+// points shared by the G lanes of a group (every lane of it calls with the
+// same cell): the cell's coefficient (v, l) is c[(v N + l) st]; h is its
 // hanging-side mask (0 on uniform grids), passed to pts.count(h) and
 // pts.row(h, i), the number of its points and the basis row of point i.
 // Every lane evaluates its share of the points, theta_1 and theta_2 come
-// from minima over the wave, and lane 0 stores the scaled modes l >= 1.
+// from minima over the group, and its first lane stores the scaled modes l >= 1
+// (nothing where neither scales).
 // Point values, theta_1 and theta_2 are formed with the same operations in
 // the same order as a single-lane loop, so the result is the same bit for
 // bit.
-template <int D, int N, class Pts>
+template <int D, int N, int G, class Pts>
 __device__ inline void positivity_cell(double *c, long st, int h, const Pts &pts, double gamma, double eps) {
   constexpr int NV = D + 2;
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & (G - 1);
   const int np = pts.count(h);
   double cf[NV][N];
 #pragma unroll
@@ -1650,14 +1658,14 @@ __device__ inline void positivity_cell(double *c, long st, int h, const Pts &pts
 #pragma unroll
     for (int l = 0; l < N; ++l) cf[v][l] = c[(long)(v * N + l) * st];
   double rmin = INFINITY;
-  for (int i = lane; i < np; i += 64) {
+  for (int i = lane; i < np; i += G) {
     const double *ph = pts.row(h, i);
     double r = 0.0;
 #pragma unroll
     for (int l = 0; l < N; ++l) r = fma(cf[0][l], ph[l], r);
     rmin = fmin(rmin, r);
   }
-  rmin = wave_min(rmin);
+  rmin = group_min<G>(rmin);
   double Ub[NV];
 #pragma unroll
   for (int v = 0; v < NV; ++v) Ub[v] = cf[v][0];
@@ -1665,7 +1673,7 @@ __device__ inline void positivity_cell(double *c, long st, int h, const Pts &pts
 #pragma unroll
   for (int l = 1; l < N; ++l) cf[0][l] *= th1;
   double th2 = 1.0;
-  for (int i = lane; i < np; i += 64) {
+  for (int i = lane; i < np; i += G) {
     const double *ph = pts.row(h, i);
     double Uq[NV];
 #pragma unroll
@@ -1682,8 +1690,8 @@ __device__ inline void positivity_cell(double *c, long st, int h, const Pts &pts
     const double pq = (gamma - 1.0) * (Uq[D + 1] - 0.5 * ke);
     if (pq < eps) th2 = fmin(th2, tau_root<D>(Ub, Uq, gamma, eps));
   }
-  th2 = wave_min(th2);
-  if (lane == 0) {
+  th2 = group_min<G>(th2);
+  if (lane == 0 && (th1 != 1.0 || th2 != 1.0)) {
 #pragma unroll
     for (int v = 0; v < NV; ++v)
 #pragma unroll
@@ -3133,7 +3141,7 @@ __global__ void k_zero_count(int *p) { p[0] = 0; }
 // The point loop of the positivity pass (Sec. 3.4) for every cell that
 // k_limit or k_limit_amr listed (those whose bounds left positivity open),
 // after those kernels have stored the cells' slope-limited coefficients: a
-// wave takes one listed cell at a time and its 64 lanes share the cell's
+// group of lanes takes one listed cell at a time and shares the cell's
 // points (positivity_cell), so a troubled cell no longer holds its whole
 // work-group while one lane walks ~150 points alone.  AMR: ids over both
 // blocks (the coarse cells, then the fine cells); a coarse cell facing the
@@ -3144,10 +3152,11 @@ __global__ __launch_bounds__(256) void k_positivity(const double *__restrict__ t
                                                     AmrGrid ag, const int *__restrict__ plist, double eps) {
   using C = Cfg<D, K>;
   constexpr int N = C::N, NW = C::NV * N, NSUB = 1 << (D - 1);
-  const long wave = ((long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const long nwaves = ((long)gridDim.x * blockDim.x) >> 6;
+  constexpr int G = pos_lanes(C::NS);
+  const long group = ((long)blockIdx.x * blockDim.x + threadIdx.x) / G;
+  const long ngroups = ((long)gridDim.x * blockDim.x) / G;
   const int cnt = plist[0];
-  for (long t = wave; t < cnt; t += nwaves) {
+  for (long t = group; t < cnt; t += ngroups) {
     const long id = plist[1 + t];
     if constexpr (!AMR) {
       struct {
@@ -3155,7 +3164,7 @@ __global__ __launch_bounds__(256) void k_positivity(const double *__restrict__ t
         __device__ int count(int) const { return C::NS; }
         __device__ const double *row(int, int i) const { return ps + i * N; }
       } pts{tab + C::PS};
-      positivity_cell<D, N>(w + id, g.ncell, 0, pts, g.gamma, eps);
+      positivity_cell<D, N, G>(w + id, g.ncell, 0, pts, g.gamma, eps);
     } else {
       const bool fine = id >= ag.ncc;
       const long cell = fine ? id - ag.ncc : id;
@@ -3189,7 +3198,7 @@ __global__ __launch_bounds__(256) void k_positivity(const double *__restrict__ t
           return t + C::HG + (f * 4 + rem / C::QF) * C::QF * N + (rem % C::QF) * N;
         }
       } pts{tab};
-      positivity_cell<D, N>(fine ? w + (long)NW * ag.ncc + cell : w + cell, fine ? ag.ncf : ag.ncc, hm, pts,
+      positivity_cell<D, N, G>(fine ? w + (long)NW * ag.ncc + cell : w + cell, fine ? ag.ncf : ag.ncc, hm, pts,
                             ag.gamma, eps);
     }
   }
@@ -3650,7 +3659,7 @@ __global__ __launch_bounds__(256) void k_limit_tree(double *__restrict__ w, Tree
 // density and pressure (<= eps) sets the flag and is left alone; a leaf whose
 // polynomial provably stays above eps everywhere in the cell (basis bounds,
 // positivity_certain: theta_1 = theta_2 = 1 exactly) needs nothing; the
-// others go to the list plist.  k_positivity_tree, one wave per listed leaf:
+// others go to the list plist.  k_positivity_tree, a group of lanes per listed leaf:
 // the points S and, on each side with finer neighbours, the leaf's trace
 // points on the two half faces (table HG; Sec. 4.4).
 template <int K>
@@ -3681,11 +3690,12 @@ __global__ __launch_bounds__(256) void k_positivity_tree(const double *__restric
                                                          TreeGrid g, const int *__restrict__ plist, double eps) {
   using C = Cfg<2, K>;
   constexpr int N = C::N;
-  const long wave = ((long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const long nwaves = ((long)gridDim.x * blockDim.x) >> 6;
+  constexpr int G = pos_lanes(C::NS);
+  const long group = ((long)blockIdx.x * blockDim.x + threadIdx.x) / G;
+  const long ngroups = ((long)gridDim.x * blockDim.x) / G;
   const long nl = g.nleaf;
   const int cnt = plist[0];
-  for (long t = wave; t < cnt; t += nwaves) {
+  for (long t = group; t < cnt; t += ngroups) {
     const long cell = plist[1 + t];
     int hm = 0;
 #pragma unroll
@@ -3707,7 +3717,7 @@ __global__ __launch_bounds__(256) void k_positivity_tree(const double *__restric
         return t + C::HG + (f * 4 + rem / C::QF) * C::QF * N + (rem % C::QF) * N;
       }
     } pts{tab};
-    positivity_cell<2, N>(w + cell, nl, hm, pts, g.gamma, eps);
+    positivity_cell<2, N, G>(w + cell, nl, hm, pts, g.gamma, eps);
   }
 }
 
@@ -4084,8 +4094,10 @@ struct LimitLaunch {
       hipLaunchKernelGGL(dg::k_zero_count, dim3(1), dim3(1), 0, s, c->plist);
       HIP_TRY(hipGetLastError());
     }
-    // waves of the point-loop kernel: a grid-stride over the listed cells
-    const unsigned npos = (unsigned)std::min<long>(1024, std::max<long>(1, (c->ncell + 255) / 256));
+    // blocks of the point-loop kernel: a grid-stride over the listed cells, about
+    // two cells for each group of lanes if every cell is listed
+    const long per = 2 * kBlock / dg::pos_lanes(c->sh.NS);
+    const unsigned npos = (unsigned)std::min<long>(1024, (c->ncell + per - 1) / per);
     if constexpr (K <= 3) {
       if (c->amr) {
         // the fine block first: its boundary cells read whole coarse polynomials
