@@ -615,6 +615,19 @@ __device__ inline void static_for(F &&f) {
   }
 }
 
+// Quadtree mesh tables (built on the host by dg_tree_set).
+struct TreeGrid {
+  long nleaf;
+  const int *lev;   // [nleaf]
+  const int *info;  // [4][nleaf]: kind | sub << 2 | ch << 3, side 2a + s (ch: kind 3's child for the limiters)
+  const int *nb;    // [8][nleaf]: neighbour (2 side + half)
+  const int *grp;   // [4][nleaf]: the four leaves of this leaf's sibling group (child order), or -1
+  double fac0;      // (2/dx) 2^-d of level 0
+  double dx0;
+  double gamma;
+  const double *t1; // 1D tables (tables_1d)
+};
+
 // Stage kernels of the other source files.  launch_line runs the stage on one
 // of them and sets *err (a hipError_t) if its rule takes the context's grid,
 // else it returns false.
@@ -623,6 +636,8 @@ bool launch_line(const dg_ctx *c, const double *w, double *out, const double *dt
 bool split2d_takes(const dg_ctx *c);
 int launch_split2d(const dg_ctx *c, const double *w, double *out, const double *dt, int mode, const Mix &mx,
                    const RateOp &ro, hipStream_t s);
+int launch_split_tree(const dg_ctx *c, const TreeGrid &g, const double *w, double *out, const double *dt, int mode,
+                      const Mix &mx, hipStream_t s);
 bool march3d_takes(const dg_ctx *c);
 int launch_march3d(const dg_ctx *c, const double *w, double *out, const double *dt, int mode, const Mix &mx,
                    hipStream_t s);

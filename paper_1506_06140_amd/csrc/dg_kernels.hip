@@ -3219,226 +3219,6 @@ __global__ __launch_bounds__(256) void k_positivity(const double *__restrict__ t
 // ===========================================================================
 namespace dg {
 
-struct TreeGrid {
-  long nleaf;
-  const int *lev;   // [nleaf]
-  const int *info;  // [4][nleaf]: kind | sub << 2 | ch << 3, side 2a + s (ch: kind 3's child for the limiters)
-  const int *nb;    // [8][nleaf]: neighbour (2 side + half)
-  const int *grp;   // [4][nleaf]: the four leaves of this leaf's sibling group (child order), or -1
-  double fac0;      // (2/dx) 2^-d of level 0
-  double dx0;
-  double gamma;
-  const double *t1; // 1D tables (tables_1d)
-};
-
-// Right-hand side and fused stage on the quadtree, one thread per leaf.
-// Volume integral as on uniform grids; each side is one face (same level,
-// wall), two half faces (finer neighbours: this leaf's trace at the mapped
-// nodes (eta + sigma)/2, lifted with w_r / 2) or one face against a coarser
-// neighbour (its trace at this leaf's half).  The contractions are
-// sum-factorised along one axis.  The total-degree basis is not a tensor product, but each of its
-// modes is P~_ex(xi) P~_ey(eta): a trace on a face normal to x is
-// sum_ey P~_ey(eta) [sum over the modes of that ey of w_l P~_ex(+-1)], the
-// lift the transpose of that, and the volume integral goes one column of
-// x-nodes at a time, contracting over ex first (tables_1d).  Both leaves of a
-// face form a trace with the same function (tree_trace), weights and tables,
-// so they obtain the same flux bit for bit.
-template <int K>
-struct Tree1D {
-  static constexpr int n1 = K + 1, PG = 0, DG = n1 * n1, GW = 2 * n1 * n1, PB = GW + n1, PH = PB + 2 * n1;
-};
-
-// values of the four variables of weights ws at the n1 nodes of a face
-// normal to axis a at xi_a = -1 (s = 0) or +1 (s = 1), the tangential node
-// coordinates' Legendre values in rows of tt ([n1][n1]); out[r][v]
-template <int K, int A>
-__device__ inline void tree_trace(const double (&ws)[4][Cfg<2, K>::N], const double *t1, int s, const double *tt,
-                                  double (&out)[K + 1][4]) {
-  using T = Tree1D<K>;
-  constexpr int N = Cfg<2, K>::N, n1 = K + 1;
-  const double *pb = t1 + T::PB + s * n1;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    double c[n1];
-#pragma unroll
-    for (int e = 0; e < n1; ++e) c[e] = 0.0;
-    static_for<0, N>([&](auto L_) {
-      // normal and tangential exponents of mode l on a face normal to axis A
-      constexpr int l = decltype(L_)::value, nrm = mode_exp<2>(l, A), tan = mode_exp<2>(l, 1 - A);
-      c[tan] = fma(ws[v][l], pb[nrm], c[tan]);
-    });
-#pragma unroll
-    for (int r = 0; r < n1; ++r) {
-      double u = 0.0;
-#pragma unroll
-      for (int e = 0; e < n1; ++e) u = fma(c[e], tt[r * n1 + e], u);
-      out[r][v] = u;
-    }
-  }
-}
-
-template <int K, int FX>
-__global__ __launch_bounds__(256) void k_rhs_tree(const double *__restrict__ tab, const double *__restrict__ w,
-                                                     double *__restrict__ out, const double *__restrict__ dtp,
-                                                     TreeGrid g, int mode, Mix mx, int *__restrict__ flag) {
-  using C = Cfg<2, K>;
-  using T = Tree1D<K>;
-  constexpr int NV = C::NV, N = C::N, n1 = K + 1;
-  const long cell = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (cell >= g.nleaf) return;
-  const long nl = g.nleaf;
-  const double gm1 = g.gamma - 1.0;
-  const double *t1 = g.t1;
-  double wc[NV][N], acc[NV][N];
-#pragma unroll
-  for (int v = 0; v < NV; ++v)
-#pragma unroll
-    for (int l = 0; l < N; ++l) {
-      wc[v][l] = w[(long)(v * N + l) * nl + cell];
-      acc[v][l] = 0.0;
-    }
-  // volume integral (eq. dg_term2), one column of x-nodes (index i) at a time
-#pragma unroll 1
-  for (int i = 0; i < n1; ++i) {
-    const double *pgi = t1 + T::PG + i * n1;
-    const double *dgi = t1 + T::DG + i * n1;
-    const double wi = t1[T::GW + i];
-    // t[v][ey] = sum over the modes of exponent ey of w_l P~_ex(g_i)
-    double tc[NV][n1], rx[NV][n1], ry[NV][n1];
-#pragma unroll
-    for (int v = 0; v < NV; ++v)
-#pragma unroll
-      for (int e = 0; e < n1; ++e) {
-        tc[v][e] = 0.0;
-        rx[v][e] = 0.0;
-        ry[v][e] = 0.0;
-      }
-#pragma unroll
-    for (int v = 0; v < NV; ++v)
-      static_for<0, N>([&](auto L_) {
-        constexpr int l = decltype(L_)::value, ex = mode_exp<2>(l, 0), ey = mode_exp<2>(l, 1);
-        tc[v][ey] = fma(wc[v][l], pgi[ex], tc[v][ey]);
-      });
-#pragma unroll 1
-    for (int j = 0; j < n1; ++j) {
-      const double *pgj = t1 + T::PG + j * n1;
-      const double *dgj = t1 + T::DG + j * n1;
-      const double wj = t1[T::GW + j];
-      double U[NV];
-#pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        double u = 0.0;
-#pragma unroll
-        for (int e = 0; e < n1; ++e) u = fma(tc[v][e], pgj[e], u);
-        U[v] = u;
-      }
-      double Fx[NV], Fy[NV];
-      euler_flux<2, double>(U, 0, gm1, Fx);
-      euler_flux<2, double>(U, 1, gm1, Fy);
-      // rx[v][ey] += F_x P~_ey(g_j) w_j,  ry[v][ey] += F_y P~_ey'(g_j) w_j
-#pragma unroll
-      for (int v = 0; v < NV; ++v)
-#pragma unroll
-        for (int e = 0; e < n1; ++e) {
-          rx[v][e] = fma(Fx[v] * wj, pgj[e], rx[v][e]);
-          ry[v][e] = fma(Fy[v] * wj, dgj[e], ry[v][e]);
-        }
-    }
-    // V_l += w_i (P~_ex'(g_i) rx[ey] + P~_ex(g_i) ry[ey])
-#pragma unroll
-    for (int v = 0; v < NV; ++v)
-      static_for<1, N>([&](auto L_) {
-        constexpr int l = decltype(L_)::value, ex = mode_exp<2>(l, 0), ey = mode_exp<2>(l, 1);
-        acc[v][l] = fma(wi, fma(dgi[ex], rx[v][ey], pgi[ex] * ry[v][ey]), acc[v][l]);
-      });
-  }
-  // face integrals (eq. dg_term3) over the sides' halves
-#pragma unroll 1
-  for (int side = 0; side < 4; ++side) {
-    const int a = side >> 1, s = side & 1;
-    const int inf = g.info[(long)side * nl + cell];
-    const int kind = inf & 3, sub = (inf >> 2) & 1;
-    const int nsub = (kind == 2) ? 2 : 1;
-#pragma unroll 1
-    for (int sb = 0; sb < nsub; ++sb) {
-      const long nbc = (kind == 1) ? cell : (long)g.nb[(long)(2 * side + sb) * nl + cell];
-      const int hs = (kind == 2) ? sb : sub;
-      const double *tto = (kind == 2) ? t1 + T::PH + hs * n1 * n1 : t1 + T::PG;
-      const double *ttn = (kind == 3) ? t1 + T::PH + hs * n1 * n1 : t1 + T::PG;
-      double Uo[n1][NV], Un[n1][NV];
-      if (a == 0)
-        tree_trace<K, 0>(wc, t1, s, tto, Uo);
-      else
-        tree_trace<K, 1>(wc, t1, s, tto, Uo);
-      {
-        double wn[NV][N];
-#pragma unroll
-        for (int v = 0; v < NV; ++v)
-#pragma unroll
-          for (int l = 0; l < N; ++l) wn[v][l] = w[(long)(v * N + l) * nl + nbc];
-        if (a == 0)
-          tree_trace<K, 0>(wn, t1, 1 - s, ttn, Un);
-        else
-          tree_trace<K, 1>(wn, t1, 1 - s, ttn, Un);
-      }
-      const double half = (kind == 2) ? 0.5 : 1.0;
-      double m[NV][n1];
-#pragma unroll
-      for (int v = 0; v < NV; ++v)
-#pragma unroll
-        for (int e = 0; e < n1; ++e) m[v][e] = 0.0;
-#pragma unroll
-      for (int r = 0; r < n1; ++r) {
-        double UL[NV], UR[NV], F[NV];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          const double un = (kind == 1) ? Uo[r][v] : Un[r][v];
-          UL[v] = s ? Uo[r][v] : un;
-          UR[v] = s ? un : Uo[r][v];
-        }
-        hllc<double, 2, FX>(UL, UR, a, g.gamma, F);
-        const double wr = half * t1[T::GW + r];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          const double f = (s ? -F[v] : F[v]) * wr;
-#pragma unroll
-          for (int e = 0; e < n1; ++e) m[v][e] = fma(f, tto[r * n1 + e], m[v][e]);
-        }
-      }
-      // lift: acc_l += P~_(normal exponent)(+-1) m[tangential exponent]
-      const double *pb = t1 + T::PB + s * n1;
-      if (a == 0) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v)
-          static_for<0, N>([&](auto L_) {
-            constexpr int l = decltype(L_)::value, en = mode_exp<2>(l, 0), et = mode_exp<2>(l, 1);
-            acc[v][l] = fma(pb[en], m[v][et], acc[v][l]);
-          });
-      } else {
-#pragma unroll
-        for (int v = 0; v < NV; ++v)
-          static_for<0, N>([&](auto L_) {
-            constexpr int l = decltype(L_)::value, en = mode_exp<2>(l, 0), et = mode_exp<2>(l, 1);
-            acc[v][l] = fma(pb[et], m[v][en], acc[v][l]);
-          });
-      }
-    }
-  }
-  const double fac = g.fac0 * (double)(1 << g.lev[cell]);
-  const double cldt = (mode == 0) ? 0.0 : mx.cl * *dtp;
-  bool bad = false;
-#pragma unroll
-  for (int v = 0; v < NV; ++v)
-#pragma unroll
-    for (int l = 0; l < N; ++l) {
-      const long ii = (long)(v * N + l) * nl + cell;
-      const double L = fac * acc[v][l];
-      bad |= (L != L);
-      out[ii] = (mode == 0) ? L : mix_out(mx, w[ii], L, cldt, ii);
-    }
-  if (bad) atomicOr(flag, FLAG_NAN);
-}
-
 // largest signal rate of the leaves' means with each leaf's own edge
 __global__ __launch_bounds__(256) void k_rate_tree(const double *__restrict__ w, TreeGrid g, int N,
                                                    unsigned long long *ratemax, int *__restrict__ flag) {
@@ -3544,43 +3324,54 @@ __global__ __launch_bounds__(256) void k_tree_nbmean(const double *__restrict__ 
   using C = Cfg<2, K>;
   constexpr int NV = C::NV, N = C::N;
   const long cell = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (plist && cell == 0) plist[0] = 0;
+  const int side = blockIdx.y;
+  if (plist && cell == 0 && side == 0) plist[0] = 0;
   if (cell >= g.nleaf) return;
   const long nl = g.nleaf;
   const int *roff = reg, *rcnt = reg + 4 * nl, *rlist = reg + 8 * nl;
-  for (int side = 0; side < 4; ++side) {
-    const int inf = g.info[(long)side * nl + cell];
-    const int kind = inf & 3, ch = (inf >> 3) & 3;
-    double m[NV];
-    if (kind == 0 || kind == 1) {
-      const long j = kind == 1 ? cell : (long)g.nb[(long)(2 * side) * nl + cell];
+  const int inf = g.info[(long)side * nl + cell];
+  const int kind = inf & 3, ch = (inf >> 3) & 3;
+  double m[NV];
+  if (kind == 0 || kind == 1) {
+    const long j = kind == 1 ? cell : (long)g.nb[(long)(2 * side) * nl + cell];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) m[v] = w[(long)(v * N) * nl + j];
-    } else if (kind == 3) {
-      const long j = g.nb[(long)(2 * side) * nl + cell];
-      const double *cm = tab + C::CM + ch * N;
+    for (int v = 0; v < NV; ++v) m[v] = w[(long)(v * N) * nl + j];
+  } else if (kind == 3) {
+    const long j = g.nb[(long)(2 * side) * nl + cell];
+    const double *cm = tab + C::CM + ch * N;
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        double s = 0.0;
+    for (int v = 0; v < NV; ++v) {
+      double s = 0.0;
 #pragma unroll
-        for (int l = 0; l < N; ++l) s = fma(w[(long)(v * N + l) * nl + j], cm[l], s);
-        m[v] = s;
-      }
-    } else {
-      const int o = roff[(long)side * nl + cell], n = rcnt[(long)side * nl + cell];
-      const int l0 = g.lev[cell];
-#pragma unroll
-      for (int v = 0; v < NV; ++v) m[v] = 0.0;
-      for (int e = 0; e < n; ++e) {
-        const long j = rlist[o + e];
-        const double frac = 1.0 / (double)(1L << (2 * (g.lev[j] - l0)));
-#pragma unroll
-        for (int v = 0; v < NV; ++v) m[v] = fma(w[(long)(v * N) * nl + j], frac, m[v]);
-      }
+      for (int l = 0; l < N; ++l) s = fma(w[(long)(v * N + l) * nl + j], cm[l], s);
+      m[v] = s;
     }
+  } else {
+    const int o = roff[(long)side * nl + cell], n = rcnt[(long)side * nl + cell];
+    const int l0 = g.lev[cell];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) nbm[(long)(side * NV + v) * nl + cell] = m[v];
+    for (int v = 0; v < NV; ++v) m[v] = 0.0;
+    // four leaves at a time, so that their indices, levels and means are in
+    // flight together; added in list order
+    for (int e0 = 0; e0 < n; e0 += 4) {
+      long j[4];
+      double frac[4], mj[4][NV];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) j[q] = rlist[o + min(e0 + q, n - 1)];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        frac[q] = 1.0 / (double)(1L << (2 * (g.lev[j[q]] - l0)));
+#pragma unroll
+        for (int v = 0; v < NV; ++v) mj[q][v] = w[(long)(v * N) * nl + j[q]];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) m[v] = e0 + q < n ? fma(mj[q][v], frac[q], m[v]) : m[v];
+    }
   }
+#pragma unroll
+  for (int v = 0; v < NV; ++v) nbm[(long)(side * NV + v) * nl + cell] = m[v];
 }
 
 // Slope limiter on a quadtree (component-wise, eq. comp_limiter, or on the
@@ -5346,13 +5137,7 @@ struct TreeStage {
   template <int K>
   int run() {
     const dg::TreeGrid g = make_tree_grid(c);
-    if (c->cfg.flux == DG_HLLC_DAVIS)
-      hipLaunchKernelGGL((dg::k_rhs_tree<K, DG_HLLC_DAVIS>), dim3(tree_blocks(g.nleaf)), dim3(kTreeBlock), 0, s,
-                         c->tab, w, out, dt, g, mode, mx, c->flag);
-    else
-      hipLaunchKernelGGL((dg::k_rhs_tree<K, DG_HLLC_BATTEN>), dim3(tree_blocks(g.nleaf)), dim3(kTreeBlock), 0, s,
-                         c->tab, w, out, dt, g, mode, mx, c->flag);
-    HIP_TRY(hipGetLastError());
+    HIP_TRY((hipError_t)dg::launch_split_tree(c, g, w, out, dt, mode, mx, s));
     return DG_OK;
   }
 };
@@ -5400,7 +5185,7 @@ struct TreeLimit {
     // the count and fill the list themselves
     int *pl = posit ? c->tplist : nullptr;
     if (c->cfg.slope_limiter != DG_LIM_NONE) {
-      hipLaunchKernelGGL((dg::k_tree_nbmean<K>), dim3(tree_blocks(g.nleaf)), dim3(kTreeBlock), 0, s, c->tab, w, g,
+      hipLaunchKernelGGL((dg::k_tree_nbmean<K>), dim3(tree_blocks(g.nleaf), 4), dim3(kTreeBlock), 0, s, c->tab, w, g,
                          c->treg, c->tnbm, pl);
       HIP_TRY(hipGetLastError());
       hipLaunchKernelGGL((c->cfg.slope_limiter == DG_LIM_CHAR ? dg::k_limit_tree<K, true> : dg::k_limit_tree<K, false>),

@@ -35,7 +35,8 @@ template <int K>
 struct Line {
   static constexpr int n1 = K + 1;
   double x[n1], w[n1], p[n1][n1], b[n1], dc[n1][n1];
-  constexpr Line() : x(), w(), p(), b(), dc() {
+  double ph[2][n1][n1];  // P~_e at (x_i - 1) / 2 and (x_i + 1) / 2: the nodes of the two halves
+  constexpr Line() : x(), w(), p(), b(), dc(), ph() {
     for (int i = 0; i < n1 / 2; ++i) {
       // bisection to the root i of P_{n1} in (0, 1), then Newton steps
       double lo = 0.0, hi = 1.0;
@@ -60,7 +61,10 @@ struct Line {
     for (int i = 0; i < n1; ++i) {
       const double d = legendre_d(n1, x[i]);
       w[i] = 2.0 / ((1.0 - x[i] * x[i]) * d * d);
-      for (int e = 0; e < n1; ++e) p[i][e] = csqrt(2 * e + 1) * legendre_p(e, x[i]);
+      for (int e = 0; e < n1; ++e) {
+        p[i][e] = csqrt(2 * e + 1) * legendre_p(e, x[i]);
+        for (int h = 0; h < 2; ++h) ph[h][i][e] = csqrt(2 * e + 1) * legendre_p(e, 0.5 * (x[i] + (h ? 1.0 : -1.0)));
+      }
     }
     for (int e = 0; e < n1; ++e) {
       b[e] = csqrt(2 * e + 1);

@@ -13,6 +13,7 @@ namespace dg {
 // state is below 4 GB), the (variable, mode) plane as the scalar offset, so a
 // load takes one vector register of address and no scalar base of its own.
 struct StateBuf {
+  using Off = unsigned;
   __amdgpu_buffer_rsrc_t r;
   unsigned plane;  // bytes of one (variable, mode) plane
   __device__ __forceinline__ StateBuf(const double *p, long nc, int planes)
@@ -31,16 +32,32 @@ struct StateBuf {
     __builtin_amdgcn_raw_buffer_store_b64(x, r, cell8, off, AUX);
   }
 };
+// A state of any size: 64-bit byte offsets.
+struct StatePtr {
+  using Off = size_t;
+  double *p;
+  Off plane;
+  __device__ __forceinline__ StatePtr(const double *q, long nc, int) : p(const_cast<double *>(q)), plane((Off)nc * 8) {}
+  template <int AUX = 0>
+  __device__ __forceinline__ double load(Off cell8, Off off) const {
+    return p[(cell8 + off) >> 3];
+  }
+  template <int AUX = 0>
+  __device__ __forceinline__ void store(double v, Off cell8, Off off) const {
+    p[(cell8 + off) >> 3] = v;
+  }
+};
 constexpr int NT = 2;  // non-temporal: data this launch touches once
 
 // the N weights of V variables of one cell, raw (off: byte offset of the first plane)
-template <int V, int N, int AUX = 0>
-__device__ __forceinline__ void load_cell(const StateBuf &w, unsigned cell8, double (&r)[V][N], unsigned off = 0) {
+template <int V, int N, int AUX = 0, class Buf>
+__device__ __forceinline__ void load_cell(const Buf &w, typename Buf::Off cell8, double (&r)[V][N],
+                                          typename Buf::Off off = 0) {
 #pragma unroll
   for (int v = 0; v < V; ++v)
 #pragma unroll
     for (int l = 0; l < N; ++l) {
-      r[v][l] = w.load<AUX>(cell8, off);
+      r[v][l] = w.template load<AUX>(cell8, off);
       off += w.plane;
     }
 }

@@ -375,6 +375,184 @@ __global__ __launch_bounds__(256, GRAV ? (K == 1 ? 4 : K == 2 ? 2 : 1) : K == 1 
   }
 }
 
+// Quadtree right-hand side and stage: five waves per 64 leaves, the volume
+// term and the fluxes of the four sides (both leaves of a face solve it, with
+// the same code and inputs), then one variable per wave as above.  A side is
+// one face (same level, wall), two half faces (finer neighbours: this leaf's
+// trace at the mapped nodes (eta + sigma)/2, the moments weighted w_r / 2) or
+// one face against a coarser neighbour (its trace at this leaf's half), so
+// each lane reads the values of P~_e at its own and its neighbour's nodes from
+// one of three tables in LDS.  Bound by the length of a wave's work (17 000
+// leaves are 270 blocks): the one-thread-per-leaf kernel it replaces issued 8 800
+// instructions one after the other.  17 296 leaves, k = 3: 57 -> 22 us (rocprofv3 means).
+template <int K, int FX, class Buf>
+__global__ __launch_bounds__(320, K <= 2 ? 3 : 2) void k_rhs_split_tree(const double *__restrict__ w,
+                                                                       double *__restrict__ out,
+                                                                       const double *__restrict__ dtp, TreeGrid g,
+                                                                       int mode, Mix mx, int *__restrict__ flag) {
+  constexpr int N = (K + 1) * (K + 2) / 2, n1 = K + 1;
+  constexpr Line<K> L{};
+  __shared__ double sv[4 * N * 64];       // volume term [v][l][lane]
+  __shared__ double sm[4 * 4 * n1 * 64];  // face moments [side][v][e][lane]
+  __shared__ double st[3 * n1 * n1];      // P~_e at the nodes of a whole face, its low half, its high half
+  const int lane = threadIdx.x & 63, role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nb = gridDim.x, xcd = blockIdx.x % 8, jb = blockIdx.x / 8;
+  const long blk = (long)xcd * (nb / 8) + min(xcd, nb % 8) + jb;
+  const long nl = g.nleaf;
+  const bool own = 64 * blk + lane < nl;
+  const unsigned leaf = (unsigned)min(64 * blk + lane, nl - 1);
+  using Off = typename Buf::Off;
+  const Off cell = (Off)8 * leaf;
+  const Buf ws(w, nl, 4 * N), os(out, nl, 4 * N);
+  if (threadIdx.x < 3 * n1 * n1) {
+    const Line<K> &T = line_const<K>();
+    const int h = threadIdx.x / (n1 * n1), r = threadIdx.x % (n1 * n1);
+    st[threadIdx.x] = h == 0 ? T.p[r / n1][r % n1] : T.ph[h - 1][r / n1][r % n1];
+  }
+  __syncthreads();
+  if (role == 0) {
+    double wc[4][N];
+    load_cell<4, N>(ws, cell, wc);
+    if constexpr (K >= 3)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int l = 0; l < N; ++l) sv[(v * N + l) * 64 + lane] = wc[v][l];
+    area_term<K, false>(
+        [&](int v, int l) __attribute__((always_inline)) {
+          if constexpr (K >= 3) return sv[(v * N + l) * 64 + lane];
+          else return wc[v][l];
+        },
+        g.gamma - 1.0, [](int, int) __attribute__((always_inline)) { return 0.0; },
+        [&](int v, const double(&r)[N]) __attribute__((always_inline)) {
+#pragma unroll
+          for (int l = 1; l < N; ++l) sv[(v * N + l) * 64 + lane] = r[l];
+        });
+  } else {
+    const int side = role - 1;
+    const int inf = g.info[(long)side * nl + leaf];
+    const int kind = inf & 3, sub = (inf >> 2) & 1;
+    const unsigned j0 = kind == 1 ? leaf : (unsigned)g.nb[(long)(2 * side) * nl + leaf];
+    const unsigned j1 = kind == 2 ? (unsigned)g.nb[(long)(2 * side + 1) * nl + leaf] : leaf;
+    double co[4][n1], m[4][n1];
+    auto face = [&](auto A_, auto S_) __attribute__((always_inline)) {
+      constexpr int A = decltype(A_)::value, S = decltype(S_)::value;
+      double cn[4][n1];
+      auto traces = [&](auto T_, Off at, double (&c)[4][n1]) __attribute__((always_inline)) {
+        constexpr int T = decltype(T_)::value;
+#pragma unroll
+        for (int v0 = 0; v0 < 4; v0 += 2) {
+          double a[2][N];
+          load_cell<2, N>(ws, at, a, (Off)(v0 * N) * ws.plane);
+#pragma unroll
+          for (int i = 0; i < 2; ++i) edge_coefs<K, A, T>(a[i], c[v0 + i]);
+        }
+      };
+      traces(S_, cell, co);
+      traces(std::integral_constant<int, 1 - S>{}, (Off)8 * j0, cn);
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int e = 0; e < n1; ++e) m[v][e] = 0.0;
+#pragma unroll 1
+      for (int sb = 0; sb < 2; ++sb) {
+        if (sb == 1) {
+          if (!__any(kind == 2)) break;
+          traces(std::integral_constant<int, 1 - S>{}, (Off)8 * j1, cn);
+        }
+        const double *to = st + (kind == 2 ? (1 + sb) * n1 * n1 : 0), *tn = st + (kind == 3 ? (1 + sub) * n1 * n1 : 0);
+        const double half = kind == 2 ? 0.5 : (sb == 0 ? 1.0 : 0.0);
+#pragma unroll
+        for (int i = 0; i < n1; ++i) {
+          double UO[4], UN[4], f[4], p[n1];
+#pragma unroll
+          for (int e = 0; e < n1; ++e) p[e] = to[i * n1 + e];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            double u = co[v][0];
+#pragma unroll
+            for (int e = 1; e < n1; ++e) u = fma(co[v][e], p[e], u);
+            UO[v] = u;
+          }
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            double u = cn[v][0];
+#pragma unroll
+            for (int e = 1; e < n1; ++e) u = fma(cn[v][e], tn[i * n1 + e], u);
+            UN[v] = kind == 1 ? UO[v] : u;
+          }
+          if constexpr (S == 1) hllc_line<2, A, FX>(UO, UN, g.gamma, f);
+          else hllc_line<2, A, FX>(UN, UO, g.gamma, f);
+          const double wr = half * L.w[i];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const double fv = sb == 0 || kind == 2 ? f[v] * wr : 0.0;
+            m[v][0] += fv;
+#pragma unroll
+            for (int e = 1; e < n1; ++e) m[v][e] = fma(fv, p[e], m[v][e]);
+          }
+          DG_FENCE;
+        }
+      }
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    if (side == 0) face(I0{}, I0{});
+    else if (side == 1) face(I0{}, I1{});
+    else if (side == 2) face(I1{}, I0{});
+    else face(I1{}, I1{});
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int e = 0; e < n1; ++e) sm[((side * 4 + v) * n1 + e) * 64 + lane] = m[v][e];
+  }
+  double wo[N], y0[N];
+  const Buf ys(mode != 0 && mx.n > 0 ? mx.y[0] : w, nl, 4 * N);
+  const int var = role < 4 ? role : 3;
+#pragma unroll
+  for (int l = 0; l < N; ++l) {
+    wo[l] = ws.load(cell, (Off)(var * N + l) * ws.plane);
+    y0[l] = ys.load(cell, (Off)(var * N + l) * ws.plane);
+  }
+  __syncthreads();
+  if (role == 4) return;
+
+  double acc[N];
+  acc[0] = 0.0;
+#pragma unroll
+  for (int l = 1; l < N; ++l) acc[l] = sv[(role * N + l) * 64 + lane];
+  auto lift = [&](auto A_, auto S_) __attribute__((always_inline)) {
+    constexpr int A = decltype(A_)::value, S = decltype(S_)::value;
+    double mm[n1];
+#pragma unroll
+    for (int e = 0; e < n1; ++e) mm[e] = sm[(((2 * A + S) * 4 + role) * n1 + e) * 64 + lane];
+    edge_lift<K, A, S>(mm, acc);
+  };
+  lift(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+  lift(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
+  lift(std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{});
+  lift(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{});
+  if (!own) return;
+  const double fac = g.fac0 * (double)(1 << g.lev[leaf]);
+  const double cldt = mode == 0 ? 0.0 : mx.cl * *dtp;
+  bool bad = false;
+  Off off = (Off)(role * N) * os.plane;
+#pragma unroll
+  for (int l = 0; l < N; ++l) {
+    const double Lv = fac * acc[l];
+    bad |= Lv != Lv;
+    double o = Lv;
+    if (mode != 0) {
+      o = fma(cldt, Lv, mx.cu * wo[l]);
+      if (mx.n > 0) o = fma(mx.a[0], y0[l], o);
+      if (mx.n > 1) o = mix_tail(mx, o, (long)(role * N + l) * nl + leaf, 1);
+    }
+    os.store(o, cell, off);
+    off += os.plane;
+  }
+  if (bad) atomicOr(flag, FLAG_NAN);
+}
+
 }  // namespace dg
 
 // FP64 on 2D grids without a refined box or a tree, unless the configuration
@@ -428,5 +606,23 @@ int dg::launch_split2d(const dg_ctx *c, const double *w, double *out, const doub
     case 3: pick(std::integral_constant<int, 3>{}); break;
     default: pick(std::integral_constant<int, 4>{}); break;
   }
+  return (int)hipGetLastError();
+}
+
+int dg::launch_split_tree(const dg_ctx *c, const TreeGrid &g, const double *w, double *out, const double *dt, int mode,
+                          const Mix &mx, hipStream_t s) {
+  const dim3 nb((unsigned)((g.nleaf + 63) / 64));
+  auto go = [&](auto K_) {
+    constexpr int K = decltype(K_)::value;
+    // 32-bit byte offsets up to 4 GB, else 64-bit ones
+    const bool big = (long long)g.nleaf * 8 * c->sh.nv * c->sh.N >= (1LL << 32);
+    const bool dav = c->cfg.flux == DG_HLLC_DAVIS;
+    auto kernel = dav ? (big ? k_rhs_split_tree<K, DG_HLLC_DAVIS, StatePtr> : k_rhs_split_tree<K, DG_HLLC_DAVIS, StateBuf>)
+                      : (big ? k_rhs_split_tree<K, DG_HLLC_BATTEN, StatePtr> : k_rhs_split_tree<K, DG_HLLC_BATTEN, StateBuf>);
+    hipLaunchKernelGGL(kernel, nb, dim3(320), 0, s, w, out, dt, g, mode, mx, c->flag);
+  };
+  if (c->sh.k == 1) go(std::integral_constant<int, 1>{});
+  else if (c->sh.k == 2) go(std::integral_constant<int, 2>{});
+  else go(std::integral_constant<int, 3>{});
   return (int)hipGetLastError();
 }
