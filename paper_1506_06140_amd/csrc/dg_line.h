@@ -247,6 +247,180 @@ __device__ __forceinline__ void hllc_line(const double (&UL)[D + 2], const doubl
   F[D + 1] = fma(e, f, fma(p, u, q * fma(Aq, Ss, B * p)));
 }
 
+// Reverse sweep of hllc_line: for the cotangent G of the flux, GL = (dF/dUL)^T
+// G and GR = (dF/dUR)^T G.  The forward values are formed with hllc_line's
+// expressions, so the same side K, bounds and star branch are taken.  The
+// sweep goes back to (rho, v, p, e = E / rho) of both sides and from there to
+// the conserved variables; no branches (a divergent one would split the
+// caller's code), a cotangent that belongs to one side only is selected for
+// L and the rest is R's.
+template <int D, int A, int FX>
+__device__ __forceinline__ void hllc_line_vjp(const double (&UL)[D + 2], const double (&UR)[D + 2], double g,
+                                              const double (&G)[D + 2], double (&GL)[D + 2], double (&GR)[D + 2]) {
+  const double gm1 = g - 1.0;
+  const double rsL = rsq3(UL[0]), rsR = rsq3(UR[0]);
+  const double irL = rsL * rsL, irR = rsR * rsR;
+  double vL[D], vR[D], keL = 0.0, keR = 0.0;  // |m|^2 / rho
+#pragma unroll
+  for (int b = 0; b < D; ++b) {
+    vL[b] = UL[1 + b] * irL;
+    vR[b] = UR[1 + b] * irR;
+    keL = fma(UL[1 + b], vL[b], keL);
+    keR = fma(UR[1 + b], vR[b], keR);
+  }
+  const double uL = vL[A], uR = vR[A];
+  const double pL = gm1 * fma(-0.5, keL, UL[D + 1]), pR = gm1 * fma(-0.5, keR, UR[D + 1]);
+  const double xL = g * pL * irL, xR = g * pR * irR;
+  const double yL = rsq3(xL), yR = rsq3(xR);
+  const double cL = xL * yL, cR = xR * yR;
+  const double eL = UL[D + 1] * irL, eR = UR[D + 1] * irR;
+  double SL, SR, is = 0.0, wL = 0.0, wR = 0.0, ct = 0.0, yt = 0.0, HL = 0.0, HR = 0.0, vt[D];
+  bool lo2, hi2;  // the bound is the second operand of its min / max
+  if constexpr (FX == DG_HLLC_DAVIS) {
+    const double a = uL - cL, b = uR - cR, c = uL + cL, d = uR + cR;
+    SL = fmin(a, b);
+    SR = fmax(c, d);
+    lo2 = b < a;
+    hi2 = d > c;
+  } else {
+    const double sL = UL[0] * rsL, sR = UR[0] * rsR;
+    is = rcp3(sL + sR);
+    wL = sL * is;
+    wR = sR * is;
+    double q2 = 0.0;
+#pragma unroll
+    for (int b = 0; b < D; ++b) {
+      vt[b] = fma(wL, vL[b], wR * vR[b]);
+      q2 = fma(vt[b], vt[b], q2);
+    }
+    HL = fma(pL, irL, eL);
+    HR = fma(pR, irR, eR);
+    const double ct2 = gm1 * fma(-0.5, q2, fma(wL, HL, wR * HR)), c2 = fmax(ct2, 1e-280);
+    const double y = rsq3(c2);
+    ct = c2 * y;
+    yt = ct2 > 0.0 ? y : 0.0;
+    const double a = uL - cL, b = vt[A] - ct, c = uR + cR, d = vt[A] + ct;
+    SL = fmin(a, b);
+    SR = fmax(c, d);
+    lo2 = b < a;
+    hi2 = d > c;
+  }
+  const double dL = SL - uL, dR = SR - uR, aL = UL[0] * dL, aR = UR[0] * dR;
+  const double num = fma(0.0, cL + cR, fma(aL, uL, fma(-aR, uR, pR - pL)));
+  const double iden = rcp3(aL - aR), Ss = num * iden;
+  const bool left = Ss >= 0.0;
+  const double S = left ? SL : SR, rho = left ? UL[0] : UR[0], u = left ? uL : uR, p = left ? pL : pR;
+  const double e = left ? eL : eR, d = S - u, iv = rcp3(S - Ss), q = Ss - u;
+  const bool star = left ? S < 0.0 : S > 0.0;
+  const double B = star ? S * iv : 0.0, rd = rho * d, Aq = B * rd, si = Ss * iv;
+  const double f = rho * (star ? d * si : u);
+
+  // F_0 = f, F_n = u f + p + Aq q, F_t = v_t f, F_E = e f + p u + q (Aq S* + B p)
+  double gf = fma(u, G[1 + A], fma(e, G[D + 1], G[0]));
+  double gv[D];  // of side K's velocities
+#pragma unroll
+  for (int b = 0; b < D; ++b)
+    if (b != A) {
+      gf = fma(left ? vL[b] : vR[b], G[1 + b], gf);
+      gv[b] = f * G[1 + b];
+    }
+  const double gE = G[D + 1], gn = G[1 + A], qE = q * gE;
+  const double ge = f * gE;
+  double gp = fma(B, qE, fma(u, gE, gn));
+  const double gA = fma(Ss, qE, q * gn);
+  const double gq = fma(Aq, gn, fma(Aq, Ss, B * p) * gE);
+  double gSs = fma(Aq, qE, gq);
+  double gu = fma(f, gn, fma(p, gE, -gq));
+  const double gB = fma(p, qE, rd * gA);
+  const double h = star ? gf : 0.0, hn = gf - h;  // the star and the plain form of f
+  double grho = fma(B * d, gA, fma(d * si, h, u * hn));
+  gu = fma(rho, hn, gu);
+  const double gd = fma(B * rho, gA, rho * si * h);
+  gSs = fma(rd * iv, h, gSs);
+  const double giv = fma(rd * Ss, h, star ? S * gB : 0.0);
+  const double tS = -iv * iv * giv;
+  double gS = (star ? iv * gB : 0.0) + gd + tS;
+  gu -= gd;
+  gSs -= tS;
+  const double gnum = gSs * iden, gden = -gnum * Ss;
+  // side K's share to L or R
+  double rL = left ? grho : 0.0, rR = grho - rL, pgL = left ? gp : 0.0, pgR = gp - pgL;
+  double sgL = left ? gS : 0.0, sgR = gS - sgL, egL = left ? ge : 0.0, egR = ge - egL;
+  double gvL[D], gvR[D];
+  gv[A] = gu;
+#pragma unroll
+  for (int b = 0; b < D; ++b) {
+    gvL[b] = left ? gv[b] : 0.0;
+    gvR[b] = gv[b] - gvL[b];
+  }
+  // S* = num / den, num = p_R - p_L + a_L u_L - a_R u_R, den = a_L - a_R, a = rho (S - u)
+  pgR += gnum;
+  pgL -= gnum;
+  const double gaL = fma(gnum, uL, gden), gaR = -fma(gnum, uR, gden);
+  rL = fma(dL, gaL, rL);
+  rR = fma(dR, gaR, rR);
+  const double tL = UL[0] * gaL, tR = UR[0] * gaR;
+  sgL += tL;
+  sgR += tR;
+  gvL[A] += fma(gnum, aL, -tL);
+  gvR[A] -= fma(gnum, aR, tR);
+  // wave-speed bounds
+  double gcL, gcR;
+  if constexpr (FX == DG_HLLC_DAVIS) {
+    const double l1 = lo2 ? 0.0 : sgL, l2 = sgL - l1, h1 = hi2 ? 0.0 : sgR, h2 = sgR - h1;
+    gvL[A] += l1 + h1;
+    gvR[A] += l2 + h2;
+    gcL = h1 - l1;
+    gcR = h2 - l2;
+  } else {
+    const double l2 = lo2 ? sgL : 0.0, l1 = sgL - l2, h2 = hi2 ? sgR : 0.0, h1 = sgR - h2;
+    gvL[A] += l1;
+    gvR[A] += h1;
+    gcL = -l1;
+    gcR = h1;
+    const double gHt = 0.5 * gm1 * (h2 - l2) * yt, gut = l2 + h2;
+    double gw = (HL - HR) * gHt;
+#pragma unroll
+    for (int b = 0; b < D; ++b) {
+      const double gb = fma(-vt[b], gHt, b == A ? gut : 0.0);
+      gw = fma(vL[b] - vR[b], gb, gw);
+      gvL[b] = fma(wL, gb, gvL[b]);
+      gvR[b] = fma(wR, gb, gvR[b]);
+    }
+    // w_L = s_L / (s_L + s_R), s = sqrt(rho)
+    const double gs = 0.5 * gw * is;
+    rL = fma(gs * wR, rsL, rL);
+    rR = fma(-gs * wL, rsR, rR);
+    // H = e + p / rho
+    const double hL = wL * gHt, hR = wR * gHt;
+    egL += hL;
+    egR += hR;
+    pgL = fma(hL, irL, pgL);
+    pgR = fma(hR, irR, pgR);
+    rL = fma(-hL * pL, irL * irL, rL);
+    rR = fma(-hR * pR, irR * irR, rR);
+  }
+  // c = sqrt(g p / rho)
+  pgL = fma(0.5 * g * irL * yL, gcL, pgL);
+  pgR = fma(0.5 * g * irR * yR, gcR, pgR);
+  rL = fma(-0.5 * cL * irL, gcL, rL);
+  rR = fma(-0.5 * cR * irR, gcR, rR);
+  // to the conserved variables: p = gm1 (E - rho |v|^2 / 2), v = m / rho, e = E / rho
+  const double kL = gm1 * pgL, kR = gm1 * pgR;
+  GL[D + 1] = fma(irL, egL, kL);
+  GR[D + 1] = fma(irR, egR, kR);
+  double sL = -eL * egL, sR = -eR * egR;
+#pragma unroll
+  for (int b = 0; b < D; ++b) {
+    sL = fma(-vL[b], gvL[b], sL);
+    sR = fma(-vR[b], gvR[b], sR);
+    GL[1 + b] = fma(irL, gvL[b], -kL * vL[b]);
+    GR[1 + b] = fma(irR, gvR[b], -kR * vR[b]);
+  }
+  GL[0] = fma(irL, sL, fma(0.5 * keL * irL, kL, rL));
+  GR[0] = fma(irR, sR, fma(0.5 * keR * irR, kR, rR));
+}
+
 // x of the lane below (lane 0 keeps its own) and of the lane above (lane 63
 // keeps its own): whole-wave DPP shifts, no LDS
 __device__ __forceinline__ double lane_below(double x) {

@@ -3,24 +3,6 @@
 
 namespace dg {
 
-// Coefficients (by tangential exponent) of the trace of w on the face normal
-// to A at xi_A = -1 (S = 0) or +1.
-template <int K, int A, int S>
-__device__ __forceinline__ void edge_coefs(const double (&w)[(K + 1) * (K + 2) / 2], double (&c)[K + 1]) {
-#pragma clang fp contract(off)
-  constexpr Line<K> L{};
-  static_for<0, K + 1>([&](auto T_) {
-    constexpr int t = decltype(T_)::value;
-    double x = w[A == 0 ? mode_index<2>(0, t, 0) : mode_index<2>(t, 0, 0)];
-    static_for<1, K + 1 - t>([&](auto N_) {
-      constexpr int n = decltype(N_)::value;
-      constexpr double s = (S == 0 && n % 2 ? -1.0 : 1.0) * L.b[n];
-      x = fma(w[A == 0 ? mode_index<2>(n, t, 0) : mode_index<2>(t, n, 0)], s, x);
-    });
-    c[t] = x;
-  });
-}
-
 // moments m[v][e] of the HLLC flux over the K + 1 face points
 template <int K, int A, int FX>
 __device__ __forceinline__ void edge_flux(const double (&cl)[4][K + 1], const double (&ch)[4][K + 1], double gamma,
