@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdg.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["dg_kernels.hip", "dg_adjoint2d.hip", "dg_line.hip", "dg_split2d.hip", "dg_march3d.hip", "dg_tables.cpp"]
+SOURCES = ["dg_kernels.hip", "dg_adjoint2d.hip", "dg_line.hip", "dg_split2d.hip", "dg_march3d.hip", "dg_split3d.hip", "dg_tables.cpp"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -640,6 +640,9 @@ int launch_split_tree(const dg_ctx *c, const TreeGrid &g, const double *w, doubl
                       const Mix &mx, hipStream_t s);
 int launch_adjoint2d(const dg_ctx *c, const double *w, const double *lam, const double *acc, double *out,
                      double *acc_out, const double *dt, int mode, double ca, double cb, hipStream_t s);
+bool split3d_takes(const dg_ctx *c);
+int launch_split3d(const dg_ctx *c, const double *w, double *out, const double *dt, int mode, const Mix &mx,
+                   hipStream_t s);
 bool march3d_takes(const dg_ctx *c);
 int launch_march3d(const dg_ctx *c, const double *w, double *out, const double *dt, int mode, const Mix &mx,
                    hipStream_t s);

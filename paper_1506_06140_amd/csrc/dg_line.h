@@ -36,7 +36,8 @@ struct Line {
   static constexpr int n1 = K + 1;
   double x[n1], w[n1], p[n1][n1], b[n1], dc[n1][n1];
   double ph[2][n1][n1];  // P~_e at (x_i - 1) / 2 and (x_i + 1) / 2: the nodes of the two halves
-  constexpr Line() : x(), w(), p(), b(), dc(), ph() {
+  double rh[n1][n1];     // P~_e((x + 1) / 2) = sum_j rh[e][j] P~_j(x), j <= e; the other half's: (-1)^(e + j) rh
+  constexpr Line() : x(), w(), p(), b(), dc(), ph(), rh() {
     for (int i = 0; i < n1 / 2; ++i) {
       // bisection to the root i of P_{n1} in (0, 1), then Newton steps
       double lo = 0.0, hi = 1.0;
@@ -69,6 +70,8 @@ struct Line {
     for (int e = 0; e < n1; ++e) {
       b[e] = csqrt(2 * e + 1);
       for (int j = 0; j < e; ++j) dc[e][j] = (e - j) % 2 ? csqrt(2 * e + 1) * csqrt(2 * j + 1) : 0.0;
+      for (int j = 0; j <= e; ++j)
+        for (int i = 0; i < n1; ++i) rh[e][j] += 0.5 * w[i] * ph[1][i][e] * p[i][j];
     }
   }
 };

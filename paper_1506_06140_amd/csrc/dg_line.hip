@@ -7,6 +7,10 @@ bool dg::launch_line(const dg_ctx *c, const double *w, double *out, const double
     *err = launch_march3d(c, w, out, dt, mode, mx, s);
     return true;
   }
+  if (ro.op == RATE_NONE && split3d_takes(c)) {
+    *err = launch_split3d(c, w, out, dt, mode, mx, s);
+    return true;
+  }
   if (split2d_takes(c)) {
     *err = launch_split2d(c, w, out, dt, mode, mx, ro, s);
     return true;

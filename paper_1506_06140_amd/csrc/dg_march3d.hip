@@ -13,107 +13,6 @@ struct MarchGrid {
   long columns;     // (nx + 2) ny ceil(nz / len)
 };
 
-// Coefficients (order of mode_index<2> in the two tangential axes, ascending)
-// of the trace of w on the face normal to A at xi_A = -1 (S = 0) or +1.
-template <int K, int A, int S>
-__device__ __forceinline__ void face_coefs(const double (&w)[(K + 1) * (K + 2) * (K + 3) / 6],
-                                  double (&c)[(K + 1) * (K + 2) / 2]) {
-#pragma clang fp contract(off)
-  constexpr Line<K> L{};
-  static_for<0, (K + 1) * (K + 2) / 2>([&](auto J_) {
-    constexpr int j = decltype(J_)::value, e1 = mode_exp<2>(j, 0), e2 = mode_exp<2>(j, 1);
-    double t = 0.0;
-    static_for<0, K + 1>([&](auto N_) {
-      constexpr int n = decltype(N_)::value;
-      if constexpr (n + e1 + e2 <= K) {
-        constexpr int l = A == 0 ? mode_index<3>(n, e1, e2) : A == 1 ? mode_index<3>(e1, n, e2) : mode_index<3>(e1, e2, n);
-        constexpr double s = S == 0 && n % 2 ? -1.0 : 1.0;
-        if constexpr (n == 0) t = w[l];
-        else t = fma(w[l], s * L.b[n], t);
-      }
-    });
-    c[j] = t;
-  });
-}
-
-// moments m[v][j] = sum_r F_v(x_r) phi_j(x_r) w_r of the HLLC flux over the
-// (K+1)^2 face points, from the two traces' coefficients (the low side's
-// through cl(v, j): they sit in LDS)
-template <int K, int A, int FX, class LO>
-__device__ __forceinline__ void face_flux(LO &&cl, const double (&ch)[5][(K + 1) * (K + 2) / 2],
-                                 double gamma, double (&m)[5][(K + 1) * (K + 2) / 2]) {
-  constexpr int n1 = K + 1, N2 = (K + 1) * (K + 2) / 2;
-  const Line<K> &T = line_const<K>();
-#pragma unroll
-  for (int v = 0; v < 5; ++v)
-#pragma unroll
-    for (int j = 0; j < N2; ++j) m[v][j] = 0.0;
-#pragma unroll 1
-  for (int r = 0; r < n1; ++r) {
-#pragma clang fp contract(off)
-    double p[n1];
-#pragma unroll
-    for (int e = 0; e < n1; ++e) p[e] = T.p[r][e];
-    const double wr = T.w[r];
-    double ul[5][n1], uh[5][n1];
-#pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      double a[n1], b[n1];
-      static_for<0, n1>([&](auto E_) {
-        constexpr int e1 = decltype(E_)::value;
-        double x = cl(v, mode_index<2>(e1, 0, 0)), y = ch[v][mode_index<2>(e1, 0, 0)];
-        static_for<1, n1 - e1>([&](auto G_) {
-          constexpr int e2 = decltype(G_)::value;
-          x = fma(cl(v, mode_index<2>(e1, e2, 0)), p[e2], x);
-          y = fma(ch[v][mode_index<2>(e1, e2, 0)], p[e2], y);
-        });
-        a[e1] = x;
-        b[e1] = y;
-      });
-      line_values<K, K>(a, ul[v]);
-      line_values<K, K>(b, uh[v]);
-      DG_FENCE;
-    }
-    double F[5][n1];
-#pragma unroll
-    for (int i = 0; i < n1; ++i) {
-      const double UL[5] = {ul[0][i], ul[1][i], ul[2][i], ul[3][i], ul[4][i]};
-      const double UR[5] = {uh[0][i], uh[1][i], uh[2][i], uh[3][i], uh[4][i]};
-      double f[5];
-      hllc_line<3, A, FX>(UL, UR, gamma, f);
-#pragma unroll
-      for (int v = 0; v < 5; ++v) F[v][i] = f[v];
-      DG_FENCE;
-    }
-#pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      double s[n1];
-      line_moments<K, K>(F[v], s);
-      static_for<0, n1>([&](auto E_) {
-        constexpr int e1 = decltype(E_)::value;
-        static_for<0, n1 - e1>([&](auto G_) {
-          constexpr int e2 = decltype(G_)::value;
-          m[v][mode_index<2>(e1, e2, 0)] = fma(s[e1], wr * p[e2], m[v][mode_index<2>(e1, e2, 0)]);
-        });
-      });
-      DG_FENCE;
-    }
-  }
-}
-
-// acc_l -+= P~_n(+-1) m_t: the outward flux of side S taken off the accumulators
-template <int K, int A, int S>
-__device__ __forceinline__ void face_lift(const double (&m)[(K + 1) * (K + 2) / 2],
-                                 double (&acc)[(K + 1) * (K + 2) * (K + 3) / 6]) {
-  constexpr Line<K> L{};
-  static_for<0, (K + 1) * (K + 2) * (K + 3) / 6>([&](auto L_) {
-    constexpr int l = decltype(L_)::value, ex = mode_exp<3>(l, 0), ey = mode_exp<3>(l, 1), ez = mode_exp<3>(l, 2);
-    constexpr int n = A == 0 ? ex : A == 1 ? ey : ez, e1 = A == 0 ? ey : ex, e2 = A == 2 ? ey : ez;
-    constexpr double s = S == 0 ? (n % 2 ? -1.0 : 1.0) : -1.0;  // low side: +F phi(-1), high side: -F phi(+1)
-    acc[l] = fma(m[mode_index<2>(e1, e2, 0)], s * L.b[n], acc[l]);
-  });
-}
-
 // Volume integral (eq. dg_term2) of one cell, added to acc: the state at the
 // Gauss nodes one axis at a time, the nine distinct non-trivial fluxes there
 // (the momentum flux tensor is symmetric), and their moments against the
