@@ -725,7 +725,7 @@ def main():
                      "alg_flops_per_launch": alg_flops, "alg_bytes_per_launch": alg_bytes,
                      "hbm_achieved_gbs": alg_bytes / (k_ms * 1e-3) / 1e9,
                      "hbm_frac": alg_bytes / (k_ms * 1e-3) / 1e9 / HBM_PEAK_GBS},
-        "limiter": {"kernel": ("k_limit<3,2,false>" if args.workload == "kh3d" else "k_limit_amr<3,3,false> (both blocks)")
+        "limiter": {"kernel": ("k_limit_comp<3,2,false>" if args.workload == "kh3d" else "k_limit_comp<3,3,true> (both blocks)")
                               + " + k_positivity",
                     "kernel_ms": lim_ms, "alg_bytes_per_launch": lim_bytes,
                     "hbm_frac": lim_bytes / (lim_ms * 1e-3) / 1e9 / HBM_PEAK_GBS},

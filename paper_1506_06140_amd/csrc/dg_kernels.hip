@@ -1768,7 +1768,8 @@ __device__ inline bool positivity_certain(const double (&wc)[D + 2][N], double g
 }
 
 // CHAR selects the characteristic limiter (eq. char_limiter) for the slope
-// pass, else the component-wise one (eq. comp_limiter).
+// pass, else the component-wise one (eq. comp_limiter; at 3D k = 2 k_limit_comp
+// runs it).
 template <int D, int K, bool CHAR>
 __global__ __launch_bounds__(256) void k_limit(const double *__restrict__ tab, double *__restrict__ w, Grid g,
                                                int slope, double beta, double bound, int posit, double eps,
@@ -2684,8 +2685,33 @@ __global__ __launch_bounds__(256) void k_amr_regrid(const double *__restrict__ w
   }
 }
 
-// Limiters on the refined mesh: neighbour means across the refinement
-// boundary are the children's average (coarse side) or the coarse polynomial's
+// Mean over child ch (bit b: the upper half along axis b) of the polynomial
+// with coefficients c(l): along each axis the mean of P~_e over (0, 1) is
+// sqrt(2e + 1) / (e (e + 1)) P_e'(0), zero for even e > 0, and the lower
+// half's has the opposite sign for odd e.  So at k = 3 in 3D 11 of the 20
+// coefficients are read and no table.
+template <int D, int N, class F>
+__device__ __forceinline__ double child_mean(F &&c, int ch) {
+  constexpr double h[4] = {1.0, 0.86602540378443864676, 0.0, -0.33071891388307382381};  // sqrt(3)/2, -sqrt(7)/8
+  double s[D], m = 0.0;
+#pragma unroll
+  for (int b = 0; b < D; ++b) s[b] = (ch >> b) & 1 ? 1.0 : -1.0;
+  static_for<0, N>([&](auto L_) {
+    constexpr int l = decltype(L_)::value, e0 = mode_exp<D>(l, 0), e1 = mode_exp<D>(l, 1), e2 = D == 3 ? mode_exp<D>(l, 2) : 0;
+    constexpr double t = h[e0] * h[e1] * h[e2];
+    if constexpr (t != 0.0) {
+      double x = c(l);
+      if constexpr (e0 % 2) x *= s[0];
+      if constexpr (e1 % 2) x *= s[1];
+      if constexpr (D == 3 && e2 % 2) x *= s[D - 1];
+      m = fma(x, t, m);
+    }
+  });
+  return m;
+}
+
+// The characteristic limiter on the refined mesh: neighbour means across the
+// refinement boundary are the children's average (coarse side) or the coarse polynomial's
 // mean over the adjacent child (fine side); coarse cells facing the fine block
 // also check positivity at the hanging-face points (k_positivity).  One
 // launch covers the ids [t0, t0 + tn) of the combined numbering (coarse
@@ -2694,13 +2720,12 @@ __global__ __launch_bounds__(256) void k_amr_regrid(const double *__restrict__ w
 // the fine block is limited first and the coarse block after it (every
 // neighbour value then comes from the state before limiting, as the
 // limiter's definition has it; means are never written).
-template <int D, int K, bool CHAR>
-__global__ __launch_bounds__(256, 2) void k_limit_amr(const double *__restrict__ tab, double *__restrict__ w, AmrGrid g,
-                                                      long t0, long tn, int slope, double beta, double mtilde,
-                                                      int posit, double eps, int *__restrict__ flag,
+template <int D, int K>
+__global__ __launch_bounds__(256, 2) void k_limit_amr(double *__restrict__ w, AmrGrid g, long t0, long tn, double beta,
+                                                      double mtilde, int posit, double eps, int *__restrict__ flag,
                                                       int *__restrict__ plist) {
   using C = Cfg<D, K>;
-  constexpr int NV = C::NV, N = C::N, NW = NV * N, NSUB = 1 << (D - 1);
+  constexpr int NV = C::NV, N = C::N, NW = NV * N;
   // lanes past the grid and on hole cells stay in the wave (the list of
   // troubled cells is appended per wave) and store nothing
   const long tid0 = t0 + (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -2715,147 +2740,8 @@ __global__ __launch_bounds__(256, 2) void k_limit_amr(const double *__restrict__
   const bool act = tid0 < t0 + tn && (fine || !amr_in_hole<D>(g, i));
   constexpr int NL = D + 1 < N ? D + 1 : N;
   const double dx = fine ? g.dxf : g.dxc;
-  if constexpr (!CHAR && D == 3 && K == 3) {
-    // component-wise at 3D k = 3: one variable at a time (only its N
-    // coefficients live, not all (D+2) N: 144 registers and three waves per
-    // SIMD instead of 256 and two; at lower degree the compiler keeps the
-    // all-variables form below in fewer registers).  Per side
-    // of the cell, once: what the neighbour mean is (0 the own mean at a
-    // wall, 1 the average of the 2^d children of a refined coarse neighbour,
-    // first child fine cell snb, 2 the mean of cell snb of block sfine,
-    // 3 the coarse polynomial of coarse cell snb over child sch)
-    int sk[2 * D], sch[2 * D];
-    long snb[2 * D];
-    bool sfine[2 * D];
-#pragma unroll
-    for (int a = 0; a < D; ++a)
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        const int f = 2 * a + s;
-        sk[f] = 0; sch[f] = 0; snb[f] = 0; sfine[f] = fine;
-        if (!fine) {
-          int j[3];
-          if (!amr_coarse_nb<D>(g, i, a, s ? 1 : -1, j)) {
-            sk[f] = 0;
-          } else if (amr_in_hole<D>(g, j)) {
-            int fi[3] = {0, 0, 0};
-#pragma unroll
-            for (int b = 0; b < D; ++b) fi[b] = 2 * (j[b] - g.lo[b]);
-            sk[f] = 1;
-            snb[f] = ((long)fi[2] * g.nf[1] + fi[1]) * g.nf[0] + fi[0];
-          } else {
-            sk[f] = 2;
-            snb[f] = ((long)j[2] * g.n[1] + j[1]) * g.n[0] + j[0];
-          }
-        } else {
-          int f2[3] = {i[0], i[1], i[2]};
-          f2[a] += s ? 1 : -1;
-          if (f2[a] >= 0 && f2[a] < g.nf[a]) {
-            sk[f] = 2;
-            snb[f] = ((long)f2[2] * g.nf[1] + f2[1]) * g.nf[0] + f2[0];
-          } else {
-            int base[3] = {0, 0, 0}, j[3];
-#pragma unroll
-            for (int b = 0; b < D; ++b) base[b] = g.lo[b] + i[b] / 2;
-            amr_coarse_nb<D>(g, base, a, s ? 1 : -1, j);
-            sk[f] = 3;
-            snb[f] = ((long)j[2] * g.n[1] + j[1]) * g.n[0] + j[0];
-            int ch = 0;
-#pragma unroll
-            for (int b = 0; b < D; ++b) ch |= ((b == a) ? (s ? 0 : 1) : (i[b] & 1)) << b;
-            sch[f] = ch;
-          }
-        }
-      }
-    const long cstr[3] = {1, (long)g.nf[0], (long)g.nf[0] * g.nf[1]};  // fine-cell strides of the children
-    // what the positivity bounds need, accumulated in variable order (the
-    // order of positivity_certain_mr): density mean and excursion, energy
-    // mean and excursion, sum (|m_a| + R_a)^2 and |m|^2
-    double m0 = 0.0, r0 = 0.0, mE = 0.0, rE = 0.0, m2 = 0.0, keb = 0.0;
-#pragma unroll 1
-    for (int v = 0; v < NV; ++v) {
-      double c[N];
-#pragma unroll
-      for (int l = 0; l < NL; ++l) c[l] = wb[(long)(v * N + l) * ncb + cell];
-      bool limited = false;
-      if (slope && K >= 1) {
-        double nbv[2 * D];
-#pragma unroll
-        for (int f = 0; f < 2 * D; ++f) {
-          double m = c[0];
-          if (sk[f] == 1) {
-            m = 0.0;
-#pragma unroll
-            for (int ch = 0; ch < (1 << D); ++ch) {
-              long o = snb[f];
-#pragma unroll
-              for (int b = 0; b < D; ++b) o += ((ch >> b) & 1) * cstr[b];
-              m += wfb[(long)(v * N) * g.ncf + o];
-            }
-            m = m / (double)(1 << D);
-          } else if (sk[f] == 2) {
-            m = sfine[f] ? wfb[(long)(v * N) * g.ncf + snb[f]] : wcb[(long)(v * N) * g.ncc + snb[f]];
-          } else if (sk[f] == 3) {
-            m = 0.0;
-#pragma unroll
-            for (int l = 0; l < N; ++l) m = fma(wcb[(long)(v * N + l) * g.ncc + snb[f]], tab[C::CM + sch[f] * N + l], m);
-          }
-          nbv[f] = m;
-        }
-        const double r3 = sqrt(3.0), bound = mtilde * dx;
-        const double mn = c[0];
-        double mt[D];
-#pragma unroll
-        for (int a = 0; a < D; ++a) {
-          const double A = r3 * c[1 + a];
-          const double m = (fabs(A) <= bound) ? A : minmod3(A, beta * (mn - nbv[2 * a]), beta * (nbv[2 * a + 1] - mn));
-          mt[a] = m;
-          limited |= (m != A);
-        }
-        if (limited) {
-#pragma unroll
-          for (int a = 0; a < D; ++a) c[1 + a] = mt[a] / r3;
-        }
-      }
-#pragma unroll
-      for (int l = NL; l < N; ++l) c[l] = limited ? 0.0 : wb[(long)(v * N + l) * ncb + cell];
-      const double Rv = basis_excursion<D, N>(c);
-      if (v == 0) {
-        m0 = c[0];
-        r0 = Rv;
-      } else if (v == NV - 1) {
-        mE = c[0];
-        rE = Rv;
-      } else {
-        const double m = fabs(c[0]) + Rv;
-        m2 = fma(m, m, m2);
-        keb = fma(c[0], c[0], keb);
-      }
-      if (act && limited) {  // an unlimited variable is unchanged in memory
-#pragma unroll
-        for (int l = 1; l < N; ++l) wb[(long)(v * N + l) * ncb + cell] = c[l];
-      }
-    }
-    if (posit) {
-      keb *= vrcp(m0);
-      const double pb = (g.gamma - 1.0) * (mE - 0.5 * keb);
-      const bool bad = !(m0 > eps) || !(pb > eps);
-      if (bad && act) atomicOr(flag, FLAG_NEGATIVE);
-      // positivity_certain_mr on the accumulated quantities
-      bool certain = false;
-      const double rlo = m0 - r0;
-      if (rlo > eps + 1e-10 * (fabs(m0) + r0)) {
-        const double ke = 0.5 * m2 / rlo;
-        const double plo = (g.gamma - 1.0) * ((mE - rE) - ke);
-        const double scale = (g.gamma - 1.0) * (fabs(mE) + rE + ke);
-        certain = plo > eps + 1e-10 * scale;
-      }
-      wave_append(act && !bad && !certain, (int)tid, plist);
-    }
-    return;
-  }
-  // characteristic: means and slopes first; the higher modes after the slope
-  // pass (as in k_limit)
+  // means and slopes first; the higher modes after the slope pass (as in
+  // k_limit)
   double wc[NV][N];
   bool dropped[NV];
 #pragma unroll
@@ -2910,44 +2796,20 @@ __global__ __launch_bounds__(256, 2) void k_limit_amr(const double *__restrict__
           for (int b = 0; b < D; ++b) ch |= ((b == a) ? (s ? 0 : 1) : (i[b] & 1)) << b;
 #pragma unroll
           for (int v = 0; v < NV; ++v) {
-            double m = 0.0;
-#pragma unroll
-            for (int l = 0; l < N; ++l) m = fma(wcb[(long)(v * N + l) * g.ncc + nb], tab[C::CM + ch * N + l], m);
-            nbm[2 * a + s][v] = m;
+            nbm[2 * a + s][v] =
+                child_mean<D, N>([&](int l) { return wcb[(long)(v * N + l) * g.ncc + nb]; }, ch);
           }
         }
       }
     }
-  if (slope && K >= 1) {
-    const double r3 = sqrt(3.0), bound = mtilde * dx;
-    if constexpr (CHAR) {
-      auto nbmean = [&](int a, int s, double *m) {
+  {
+    auto nbmean = [&](int a, int s, double *m) {
 #pragma unroll
-        for (int v = 0; v < NV; ++v) m[v] = nbm[2 * a + s][v];
-      };
-      const bool lim = char_limit_cell<D, N>(wc, nbmean, g.gamma, beta, bound);
+      for (int v = 0; v < NV; ++v) m[v] = nbm[2 * a + s][v];
+    };
+    const bool lim = char_limit_cell<D, N>(wc, nbmean, g.gamma, beta, mtilde * dx);
 #pragma unroll
-      for (int v = 0; v < NV; ++v) dropped[v] = lim;
-    } else
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      const double mean = wc[v][0];
-      double mt[D];
-      bool limited = false;
-#pragma unroll
-      for (int a = 0; a < D; ++a) {
-        const double A = r3 * wc[v][1 + a];
-        const double m = (fabs(A) <= bound) ? A
-                                            : minmod3(A, beta * (mean - nbm[2 * a][v]), beta * (nbm[2 * a + 1][v] - mean));
-        mt[a] = m;
-        limited |= (m != A);
-      }
-      if (limited) {
-#pragma unroll
-        for (int a = 0; a < D; ++a) wc[v][1 + a] = mt[a] / r3;
-      }
-      dropped[v] = limited;
-    }
+    for (int v = 0; v < NV; ++v) dropped[v] = lim;
   }
 #pragma unroll
   for (int v = 0; v < NV; ++v)
@@ -2974,6 +2836,170 @@ __global__ __launch_bounds__(256, 2) void k_limit_amr(const double *__restrict__
       if (dropped[v])
 #pragma unroll
         for (int l = 1; l < N; ++l) wb[(long)(v * N + l) * ncb + cell] = wc[v][l];
+  }
+}
+
+// The component-wise limiter (eq. comp_limiter) and the positivity bounds on
+// the refined box (k_limit_amr's launches and neighbour means) and on 3D
+// uniform grids at k = 2.  A variable's limiter needs that variable alone, so a
+// workgroup is 64 cells with one wave per variable: all of a wave's loads (the
+// cell's N coefficients and its 2d neighbour means) are in flight at once, and
+// the few lanes of a wave that need a mean across the refinement boundary cost
+// one variable's loads, once per axis.  The means and excursions meet in LDS,
+// where the first wave decides which cells go to k_positivity's list.
+// slope = 0: the positivity bounds alone.
+// Bound by HBM: the state is read once, limited variables are written.  The
+// whole pass, one thread per cell before (with a pass and the table of child
+// means for either side): 64^3 box k = 3 225 -> 140 us (a blast's, with a
+// third of the cells limited, 250 -> 147 without k_positivity), 16^3 68 -> 16;
+// 96 x 96 x 64 box k = 2 314 -> 161, k = 1 129 -> 84; 256^2 box k = 3 40 -> 17;
+// uniform 128^3 k = 2 218 -> 194, 32^3 9.0 -> 7.9.  On the other uniform grids
+// one thread per cell stays (2D k = 3 512^2 18.0 against 19.8 here; 3D k = 1
+// 128^3 70, 96; k = 3 100^3 137, 168): there its loads were in flight together
+// already and this form's many short waves cost more than its parallelism.
+template <int D, int K, bool AMR>
+__global__ __launch_bounds__(64 * (D + 2)) void k_limit_comp(double *__restrict__ w, Grid g, AmrGrid ag, long t0,
+                                                             long tn, int slope, double beta, double mtilde, int posit,
+                                                             double eps, int *__restrict__ flag,
+                                                             int *__restrict__ plist) {
+  using C = Cfg<D, K>;
+  constexpr int NV = C::NV, N = C::N;
+  __shared__ double sm[NV * 64], sr[NV * 64];
+  const int lane = threadIdx.x & 63, v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // XCD b mod 8 takes a contiguous band of the cells: a plane's means are read
+  // for the cells on its other sides from the same L2
+  const int nb = gridDim.x, xcd = blockIdx.x % 8;
+  const long blk = (long)xcd * (nb / 8) + min(xcd, nb % 8) + blockIdx.x / 8;
+  const long tid0 = t0 + blk * 64 + lane, tid = min(tid0, t0 + tn - 1);
+  bool act = tid0 < t0 + tn;
+  double nbv[2 * D], c[N];
+  double *wv;  // this block's variable v
+  long nc, cell;
+  double dx;
+  if constexpr (AMR) {
+    const bool fine = t0 >= ag.ncc;  // uniform: a launch covers one block
+    nc = fine ? ag.ncf : ag.ncc;
+    cell = fine ? tid - ag.ncc : tid;
+    const double *cv = w + (long)(v * N) * ag.ncc, *fv = w + (long)(NV * N) * ag.ncc + (long)(v * N) * ag.ncf;
+    wv = const_cast<double *>(fine ? fv : cv);
+    dx = fine ? ag.dxf : ag.dxc;
+    const int n0 = fine ? ag.nf[0] : ag.n[0], n1 = fine ? ag.nf[1] : ag.n[1];
+    const int i[3] = {(int)(cell % n0), (int)((cell / n0) % n1), (int)(cell / ((long)n0 * n1))};
+    act = act && (fine || !amr_in_hole<D>(ag, i));
+#pragma unroll
+    for (int l = 0; l < N; ++l) c[l] = wv[(long)l * nc + cell];
+    if (slope) {
+#pragma unroll
+      for (int a = 0; a < D; ++a) {
+        long o[2] = {cell, cell};
+        int special = -1, j[3];  // the side (at most one) whose mean is not a cell's
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          int j2[3] = {i[0], i[1], i[2]};
+          if (!fine) {
+            if (amr_coarse_nb<D>(ag, i, a, s ? 1 : -1, j2)) {
+              o[s] = ((long)j2[2] * n1 + j2[1]) * n0 + j2[0];
+              if (amr_in_hole<D>(ag, j2)) {
+                special = s;
+                j[0] = j2[0]; j[1] = j2[1]; j[2] = j2[2];
+              }
+            }
+          } else {
+            j2[a] += s ? 1 : -1;
+            if (j2[a] >= 0 && j2[a] < ag.nf[a]) {
+              o[s] = ((long)j2[2] * n1 + j2[1]) * n0 + j2[0];
+            } else {
+              special = s;
+#pragma unroll
+              for (int b = 0; b < 3; ++b) j[b] = b < D ? ag.lo[b] + (j2[b] >> 1) : 0;
+            }
+          }
+          nbv[2 * a + s] = wv[o[s]];
+        }
+        if (special >= 0) {
+          double m;
+          if (!fine) {  // the children's average
+            m = 0.0;
+#pragma unroll
+            for (int ch = 0; ch < (1 << D); ++ch) {
+              int f[3] = {0, 0, 0};
+#pragma unroll
+              for (int b = 0; b < D; ++b) f[b] = 2 * (j[b] - ag.lo[b]) + ((ch >> b) & 1);
+              m += fv[((long)f[2] * ag.nf[1] + f[1]) * ag.nf[0] + f[0]];
+            }
+            m = m / (double)(1 << D);
+          } else {  // the coarse polynomial over the child beside this cell
+            int ch = 0;
+#pragma unroll
+            for (int b = 0; b < D; ++b) ch |= ((b == a) ? (special ? 0 : 1) : (i[b] & 1)) << b;
+            const long oc = ((long)j[2] * ag.n[1] + j[1]) * ag.n[0] + j[0];
+            m = child_mean<D, N>([&](int l) { return cv[(long)l * ag.ncc + oc]; }, ch);
+          }
+          nbv[2 * a + 1] = special == 1 ? m : nbv[2 * a + 1];
+          nbv[2 * a] = special == 0 ? m : nbv[2 * a];
+        }
+      }
+    }
+  } else {
+    nc = g.ncell;
+    cell = tid;
+    wv = w + (long)(v * N) * nc;
+    dx = 1.0;  // mtilde is the bound itself
+    const int ix = (int)(cell % g.nx), iy = (int)((cell / g.nx) % g.ny), iz = (int)(cell / ((long)g.nx * g.ny));
+#pragma unroll
+    for (int l = 0; l < N; ++l) c[l] = wv[(long)l * nc + cell];
+    if (slope) {
+#pragma unroll
+      for (int a = 0; a < D; ++a)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const long o = neighbour(g, ix, iy, iz, a, s ? 1 : -1);
+          nbv[2 * a + s] = wv[o < 0 ? cell : o];
+        }
+    }
+  }
+  bool limited = false;
+  if (slope) {
+    const double r3 = sqrt(3.0), bound = mtilde * dx, mean = c[0];
+    double mt[D];
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+      const double A = r3 * c[1 + a];
+      const double m = (fabs(A) <= bound) ? A : minmod3(A, beta * (mean - nbv[2 * a]), beta * (nbv[2 * a + 1] - mean));
+      mt[a] = m;
+      limited |= (m != A);
+    }
+#pragma unroll
+    for (int a = 0; a < D; ++a) c[1 + a] = limited ? mt[a] / r3 : c[1 + a];
+#pragma unroll
+    for (int l = D + 1; l < N; ++l) c[l] = limited ? 0.0 : c[l];
+    if (act && limited) {  // an unlimited variable is unchanged in memory (the means always)
+#pragma unroll
+      for (int l = 1; l < N; ++l) wv[(long)l * nc + cell] = c[l];
+    }
+  }
+  if (posit) {
+    sm[v * 64 + lane] = c[0];
+    sr[v * 64 + lane] = basis_excursion<D, N>(c);
+    __syncthreads();
+    if (v == 0) {
+      double Ub[NV], R[NV], keb = 0.0;
+#pragma unroll
+      for (int u = 0; u < NV; ++u) {
+        Ub[u] = sm[u * 64 + lane];
+        R[u] = sr[u * 64 + lane];
+      }
+#pragma unroll
+      for (int b = 0; b < D; ++b) keb = fma(Ub[1 + b], Ub[1 + b], keb);
+      const double gam = AMR ? ag.gamma : g.gamma;
+      keb *= vrcp(Ub[0]);
+      const double pb = (gam - 1.0) * (Ub[D + 1] - 0.5 * keb);
+      const bool bad = !(Ub[0] > eps) || !(pb > eps);
+      if (bad && act) atomicOr(flag, FLAG_NEGATIVE);
+      // a cell whose bounds leave positivity open goes to k_positivity's list
+      // (ids of the box: the coarse cells, then the fine cells)
+      wave_append(act && !bad && !positivity_certain_mr<D>(Ub, R, gam, eps), (int)tid, plist);
+    }
   }
 }
 
@@ -3735,9 +3761,14 @@ struct LimitLaunch {
         // the fine block first: its boundary cells read whole coarse polynomials
         const long part[2][2] = {{c->ncc, c->ncf}, {0, c->ncc}};
         for (const auto &pt : part) {
-          hipLaunchKernelGGL((chr ? dg::k_limit_amr<D, K, true> : dg::k_limit_amr<D, K, false>),
-                             dim3(nblocks(pt[1])), dim3(kBlock), 0, s, c->tab, w, make_amr_grid(c), pt[0], pt[1],
-                             slope, c->cfg.beta, c->cfg.m_tilde, posit, c->cfg.eps, c->flag, c->plist);
+          if (chr)
+            hipLaunchKernelGGL((dg::k_limit_amr<D, K>), dim3(nblocks(pt[1])), dim3(kBlock), 0, s, w,
+                               make_amr_grid(c), pt[0], pt[1], c->cfg.beta, c->cfg.m_tilde, posit, c->cfg.eps, c->flag,
+                               c->plist);
+          else
+            hipLaunchKernelGGL((dg::k_limit_comp<D, K, true>), dim3((unsigned)((pt[1] + 63) / 64)),
+                               dim3(64 * (D + 2)), 0, s, w, dg::Grid{}, make_amr_grid(c), pt[0], pt[1], slope,
+                               c->cfg.beta, c->cfg.m_tilde, posit, c->cfg.eps, c->flag, c->plist);
           HIP_TRY(hipGetLastError());
         }
         if (posit)
@@ -3747,9 +3778,20 @@ struct LimitLaunch {
         return DG_OK;
       }
     }
-    hipLaunchKernelGGL((chr ? dg::k_limit<D, K, true> : dg::k_limit<D, K, false>), dim3(nblocks(c->ncell)),
-                       dim3(kBlock), 0, s, c->tab, w, make_grid(c), slope, c->cfg.beta, c->cfg.m_tilde * c->dx,
-                       posit, c->cfg.eps, c->flag, c->plist);
+    if constexpr (D == 3 && K == 2) {
+      if (chr)
+        hipLaunchKernelGGL((dg::k_limit<D, K, true>), dim3(nblocks(c->ncell)), dim3(kBlock), 0, s, c->tab, w,
+                           make_grid(c), slope, c->cfg.beta, c->cfg.m_tilde * c->dx, posit, c->cfg.eps, c->flag,
+                           c->plist);
+      else
+        hipLaunchKernelGGL((dg::k_limit_comp<D, K, false>), dim3((unsigned)((c->ncell + 63) / 64)),
+                           dim3(64 * (D + 2)), 0, s, w, make_grid(c), dg::AmrGrid{}, 0L, c->ncell, slope, c->cfg.beta,
+                           c->cfg.m_tilde * c->dx, posit, c->cfg.eps, c->flag, c->plist);
+    } else {
+      hipLaunchKernelGGL((chr ? dg::k_limit<D, K, true> : dg::k_limit<D, K, false>), dim3(nblocks(c->ncell)),
+                         dim3(kBlock), 0, s, c->tab, w, make_grid(c), slope, c->cfg.beta, c->cfg.m_tilde * c->dx,
+                         posit, c->cfg.eps, c->flag, c->plist);
+    }
     HIP_TRY(hipGetLastError());
     if (posit)
       hipLaunchKernelGGL((dg::k_positivity<D, K, false>), dim3(npos), dim3(kBlock), 0, s, c->tab, w, make_grid(c),
