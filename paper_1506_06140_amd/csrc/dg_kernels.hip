@@ -22,7 +22,6 @@
 #include <new>
 #include <type_traits>
 #include <algorithm>
-#include <unordered_map>
 #include <utility>
 #include <vector>
 
@@ -4660,10 +4659,45 @@ inline uint64_t tkey(int l, long x, long y) { return ((uint64_t)l << 58) | ((uin
 
 constexpr int kTreeInts = 17;  // per leaf: level, 4 face infos, 8 neighbours, 4 group members
 
+// Leaf of a (level, x, y) key: open addressing with linear probes in one array
+// of twice the leaves or more (a node-based map spent most of an adaptation's
+// host time in its lookups and allocations).
 struct TreeIndex {
-  std::unordered_map<uint64_t, int> m;
+  struct Slot {
+    uint64_t key;
+    int leaf;
+  };
+  static constexpr uint64_t kFree = ~0ull;  // no key: levels end at 24
+  std::vector<Slot> slot;
+  int shift = 0;
   long nx = 0, ny = 0;
   int bc[2] = {0, 0};
+  void init(const dg_ctx *c, long nl) {
+    int bits = 4;
+    while ((1L << bits) < 2 * nl) ++bits;
+    slot.assign((size_t)1 << bits, Slot{kFree, -1});
+    shift = 64 - bits;
+    nx = c->nx;
+    ny = c->ny;
+    bc[0] = c->cfg.bc[0];
+    bc[1] = c->cfg.bc[1];
+  }
+  // the key's slot, or the free one where it belongs (a mixed product: x and y
+  // of neighbouring leaves spread over the array)
+  size_t at(uint64_t key) const {
+    uint64_t h = key * 0x9e3779b97f4a7c15ull;
+    h ^= h >> 32;
+    size_t i = (size_t)((h * 0x9e3779b97f4a7c15ull) >> shift);
+    while (slot[i].key != key && slot[i].key != kFree) i = (i + 1) & (slot.size() - 1);
+    return i;
+  }
+  // false if the key is there already
+  bool add(uint64_t key, int leaf) {
+    Slot &e = slot[at(key)];
+    if (e.key == key) return false;
+    e = Slot{key, leaf};
+    return true;
+  }
   // level-l cell (x, y) wrapped onto the periodic domain; false outside a wall
   bool wrap(int l, long &x, long &y) const {
     const long nxl = nx << l, nyl = ny << l;
@@ -4678,8 +4712,7 @@ struct TreeIndex {
     return true;
   }
   int find(int l, long x, long y) const {
-    auto it = m.find(tkey(l, x, y));
-    return it == m.end() ? -1 : it->second;
+    return slot[at(tkey(l, x, y))].leaf;
   }
   // the leaf that covers level-l cell (x, y) if it is that cell or coarser, else -1
   int covering(int l, long x, long y) const {
@@ -4691,25 +4724,18 @@ struct TreeIndex {
   }
 };
 
-// Validates a leaf set (a tiling of the base grid, the level jump across every
-// face at most one) and builds its device tables: level [nl], face info
-// [4][nl] (kind | sub << 2), neighbours [8][nl], sibling groups [4][nl].
-int tree_tables(const dg_ctx *c, const std::vector<int32_t> &lv, TreeIndex &ix, std::vector<int> &T) {
+// Validates a leaf set (a tiling of the base grid) and indexes it.
+int tree_index(const dg_ctx *c, const std::vector<int32_t> &lv, TreeIndex &ix) {
   const long nl = (long)lv.size() / 3;
   if (nl < 1 || nl > (1L << 30)) return DG_EINVAL;
-  ix.m.clear();
-  ix.m.reserve((size_t)nl * 2);
-  ix.nx = c->nx;
-  ix.ny = c->ny;
-  ix.bc[0] = c->cfg.bc[0];
-  ix.bc[1] = c->cfg.bc[1];
+  ix.init(c, nl);
   int L = 0;
   for (long i = 0; i < nl; ++i) {
     const int l = lv[3 * i];
     const long x = lv[3 * i + 1], y = lv[3 * i + 2];
     if (l < 0 || l > 24 || (c->nx << l) >= (1L << 29) || (c->ny << l) >= (1L << 29)) return DG_EINVAL;
     if (x < 0 || y < 0 || x >= (c->nx << l) || y >= (c->ny << l)) return DG_EINVAL;
-    if (!ix.m.emplace(tkey(l, x, y), (int)i).second) return DG_EINVAL;
+    if (!ix.add(tkey(l, x, y), (int)i)) return DG_EINVAL;
     L = l > L ? l : L;
   }
   unsigned __int128 area = 0;
@@ -4720,6 +4746,28 @@ int tree_tables(const dg_ctx *c, const std::vector<int32_t> &lv, TreeIndex &ix, 
     area += (unsigned __int128)1 << (2 * (L - l));
   }
   if (area != ((unsigned __int128)(c->nx * c->ny) << (2 * L))) return DG_EINVAL;
+  return DG_OK;
+}
+
+// the leaves of the sibling group of level-l cell (x, y), in child order;
+// false unless all four are there
+bool tree_group(const TreeIndex &ix, int l, long x, long y, int (&g)[4]) {
+  if (l < 1) return false;
+  bool all = true;
+  for (int ch = 0; ch < 4 && all; ++ch) {
+    g[ch] = ix.find(l, 2 * (x >> 1) + (ch & 1), 2 * (y >> 1) + (ch >> 1));
+    all = g[ch] >= 0;
+  }
+  return all;
+}
+
+// Validates a leaf set (a tiling, the level jump across every face at most
+// one) and builds its device tables: level [nl], face info [4][nl] (kind |
+// sub << 2), neighbours [8][nl], sibling groups [4][nl].
+int tree_tables(const dg_ctx *c, const std::vector<int32_t> &lv, TreeIndex &ix, std::vector<int> &T) {
+  const int st = tree_index(c, lv, ix);
+  if (st != DG_OK) return st;
+  const long nl = (long)lv.size() / 3;
   T.assign((size_t)kTreeInts * nl, -1);
   int *lev = T.data(), *info = lev + nl, *nb = info + 4 * nl, *grp = nb + 8 * nl;
   for (long i = 0; i < nl; ++i) {
@@ -4751,16 +4799,9 @@ int tree_tables(const dg_ctx *c, const std::vector<int32_t> &lv, TreeIndex &ix, 
       nb[(long)(2 * side) * nl + i] = n0;
       nb[(long)(2 * side + 1) * nl + i] = n1;
     }
-    if (l > 0) {
-      int g[4];
-      bool all = true;
-      for (int ch = 0; ch < 4; ++ch) {
-        g[ch] = ix.find(l, 2 * (x >> 1) + (ch & 1), 2 * (y >> 1) + (ch >> 1));
-        all &= g[ch] >= 0;
-      }
-      if (all)
-        for (int ch = 0; ch < 4; ++ch) grp[(long)ch * nl + i] = g[ch];
-    }
+    int g[4];
+    if (tree_group(ix, l, x, y, g))
+      for (int ch = 0; ch < 4; ++ch) grp[(long)ch * nl + i] = g[ch];
   }
   return DG_OK;
 }
@@ -4820,27 +4861,32 @@ int tree_upload(dg_ctx *c, std::vector<int32_t> &lv, TreeIndex &ix, const std::v
   // limiters: per side with finer neighbours the leaves inside the same-level
   // cell there, in leaf order ([4][nl] offsets, [4][nl] counts, the lists)
   const long nl = (long)lv.size() / 3;
-  std::vector<int> R((size_t)8 * nl, 0);
+  std::vector<int> R((size_t)8 * nl, 0), in;
+  R.reserve((size_t)10 * nl);
   const int *info = T.data() + nl;
+  struct Cell {
+    int l;
+    long x, y;
+  };
+  Cell todo[4 * 25];  // a level adds at most three to the stack
   for (long i = 0; i < nl; ++i)
     for (int side = 0; side < 4; ++side) {
       if ((info[(long)side * nl + i] & 3) != 2) continue;
       const int a = side >> 1, sd = side & 1, l = lv[3 * i];
       long X = lv[3 * i + 1] + (a == 0 ? (sd ? 1 : -1) : 0), Y = lv[3 * i + 2] + (a == 1 ? (sd ? 1 : -1) : 0);
       ix.wrap(l, X, Y);
-      std::vector<int> in;
-      std::vector<std::pair<int, std::pair<long, long>>> st{{l, {X, Y}}};
-      while (!st.empty()) {
-        const auto e = st.back();
-        st.pop_back();
-        const int j = ix.find(e.first, e.second.first, e.second.second);
+      in.clear();
+      int n = 0;
+      todo[n++] = {l, X, Y};
+      while (n > 0) {
+        const Cell e = todo[--n];
+        const int j = ix.find(e.l, e.x, e.y);
         if (j >= 0) {
           in.push_back(j);
           continue;
         }
-        if (e.first >= 24) return DG_EINVAL;
-        for (int ch = 0; ch < 4; ++ch)
-          st.push_back({e.first + 1, {2 * e.second.first + (ch & 1), 2 * e.second.second + (ch >> 1)}});
+        if (e.l >= 24) return DG_EINVAL;
+        for (int ch = 0; ch < 4; ++ch) todo[n++] = {e.l + 1, 2 * e.x + (ch & 1), 2 * e.y + (ch >> 1)};
       }
       std::sort(in.begin(), in.end());
       R[(size_t)(side * nl + i)] = (int)(R.size() - 8 * nl);
@@ -4865,29 +4911,45 @@ int tree_upload(dg_ctx *c, std::vector<int32_t> &lv, TreeIndex &ix, const std::v
   return DG_OK;
 }
 
-// Morton order of the leaves' lower-left corners on the finest level
-void tree_sort(std::vector<int32_t> &lv, std::vector<int> *perm_src = nullptr) {
+// the bits of x in the even places
+inline uint64_t spread_bits(uint64_t x) {
+  x = (x | (x << 16)) & 0x0000ffff0000ffffull;
+  x = (x | (x << 8)) & 0x00ff00ff00ff00ffull;
+  x = (x | (x << 4)) & 0x0f0f0f0f0f0f0f0full;
+  x = (x | (x << 2)) & 0x3333333333333333ull;
+  return (x | (x << 1)) & 0x5555555555555555ull;
+}
+
+// Morton order of the leaves' lower-left corners on the finest level, as a
+// permutation: a radix sort over the keys' bits (coordinates there are below
+// 2^30: a mesh's are below 2^29 and one adaptation adds one level)
+std::vector<int> tree_order(const std::vector<int32_t> &lv) {
   const long nl = (long)lv.size() / 3;
   int L = 0;
   for (long i = 0; i < nl; ++i) L = lv[3 * i] > L ? lv[3 * i] : L;
-  std::vector<std::pair<unsigned __int128, long>> keys((size_t)nl);
+  struct Key {
+    uint64_t k;
+    int i;
+  };
+  std::vector<Key> a((size_t)nl), b((size_t)nl);
+  uint64_t any = 0;
   for (long i = 0; i < nl; ++i) {
-    const uint64_t x = (uint64_t)lv[3 * i + 1] << (L - lv[3 * i]), y = (uint64_t)lv[3 * i + 2] << (L - lv[3 * i]);
-    unsigned __int128 k = 0;
-    for (int b = 0; b < 60; ++b)
-      k |= ((unsigned __int128)((x >> b) & 1) << (2 * b)) | ((unsigned __int128)((y >> b) & 1) << (2 * b + 1));
-    keys[(size_t)i] = {k, i};
+    const int up = L - lv[3 * i];
+    const uint64_t k = spread_bits((uint64_t)lv[3 * i + 1] << up) | (spread_bits((uint64_t)lv[3 * i + 2] << up) << 1);
+    a[(size_t)i] = {k, (int)i};
+    any |= k;
   }
-  std::sort(keys.begin(), keys.end());
-  std::vector<int32_t> out(lv.size());
-  std::vector<int> ps;
-  for (long j = 0; j < nl; ++j) {
-    const long i = keys[(size_t)j].second;
-    for (int e = 0; e < 3; ++e) out[3 * j + e] = lv[3 * i + e];
-    ps.push_back((int)i);
+  constexpr int kBits = 11;
+  for (int sh = 0; sh < 64 && (any >> sh) != 0; sh += kBits) {
+    long count[(1 << kBits) + 1] = {};
+    for (const Key &e : a) ++count[((e.k >> sh) & ((1 << kBits) - 1)) + 1];
+    for (int d = 0; d < (1 << kBits); ++d) count[d + 1] += count[d];
+    for (const Key &e : a) b[(size_t)count[(e.k >> sh) & ((1 << kBits) - 1)]++] = e;
+    a.swap(b);
   }
-  lv.swap(out);
-  if (perm_src) *perm_src = ps;
+  std::vector<int> perm((size_t)nl);
+  for (long j = 0; j < nl; ++j) perm[(size_t)j] = a[(size_t)j].i;
+  return perm;
 }
 
 // The next mesh from the current leaves and their flags (k_tree_flags):
@@ -4905,8 +4967,7 @@ int tree_plan(const dg_ctx *c, const std::vector<int> &flags, int max_level, std
   const std::vector<int32_t> &lv = c->tleaves;
   const long nl = (long)lv.size() / 3;
   TreeIndex ix;
-  std::vector<int> T;
-  int st = tree_tables(c, lv, ix, T);
+  const int st = tree_index(c, lv, ix);
   if (st != DG_OK) return st;
   auto L = [&](long i) { return lv[3 * i]; };
   auto X = [&](long i) { return (long)lv[3 * i + 1]; };
@@ -4944,11 +5005,11 @@ int tree_plan(const dg_ctx *c, const std::vector<int> &flags, int max_level, std
   std::vector<char> merge((size_t)nl, 0);
   for (long i = 0; i < nl; ++i) {
     if (!(flags[(size_t)i] & 4) || (flags[(size_t)i] & 2) || L(i) < 1) continue;
-    const int *grp = T.data() + 13 * nl;
-    if (grp[i] != i) continue;  // the group's child 0 decides
+    int grp[4];
+    if ((X(i) & 1) || (Y(i) & 1) || !tree_group(ix, L(i), X(i), Y(i), grp)) continue;  // the group's child 0 decides
     bool ok = true;
     for (int ch = 0; ch < 4 && ok; ++ch) {
-      const long m = grp[(long)ch * nl + i];
+      const long m = grp[ch];
       if (split[(size_t)m] || (flags[(size_t)m] & 2)) { ok = false; break; }
       for (int dx = -1; dx <= 1 && ok; ++dx)
         for (int dy = -1; dy <= 1 && ok; ++dy) {
@@ -4958,11 +5019,14 @@ int tree_plan(const dg_ctx *c, const std::vector<int> &flags, int max_level, std
         }
     }
     if (ok)
-      for (int ch = 0; ch < 4; ++ch) merge[(size_t)grp[(long)ch * nl + i]] = 1;
+      for (int ch = 0; ch < 4; ++ch) merge[(size_t)grp[ch]] = 1;
   }
   // new leaves with their sources, then Morton order
   std::vector<int32_t> nx;
   std::vector<int> k0, s0;  // kind | child << 2, and 4 sources
+  nx.reserve((size_t)6 * nl);
+  k0.reserve((size_t)2 * nl);
+  s0.reserve((size_t)8 * nl);
   for (long i = 0; i < nl; ++i) {
     if (split[(size_t)i]) {
       for (int ch = 0; ch < 4; ++ch) {
@@ -4971,28 +5035,28 @@ int tree_plan(const dg_ctx *c, const std::vector<int> &flags, int max_level, std
         s0.insert(s0.end(), {(int)i, -1, -1, -1});
       }
     } else if (merge[(size_t)i]) {
-      const int *grp = T.data() + 13 * nl;
-      if (grp[i] != i) continue;
+      int grp[4];
+      if (!tree_group(ix, L(i), X(i), Y(i), grp) || grp[0] != i) continue;
       nx.insert(nx.end(), {L(i) - 1, (int32_t)(X(i) >> 1), (int32_t)(Y(i) >> 1)});
       k0.push_back(2);
-      s0.insert(s0.end(), {grp[i], grp[nl + i], grp[2 * nl + i], grp[3 * nl + i]});
+      s0.insert(s0.end(), {grp[0], grp[1], grp[2], grp[3]});
     } else {
       nx.insert(nx.end(), {L(i), (int32_t)X(i), (int32_t)Y(i)});
       k0.push_back(0);
       s0.insert(s0.end(), {(int)i, -1, -1, -1});
     }
   }
-  std::vector<int> perm;
-  tree_sort(nx, &perm);
+  const std::vector<int> perm = tree_order(nx);
   const long nn = (long)perm.size();
-  rk.assign((size_t)nn, 0);
-  src.assign((size_t)4 * nn, -1);
+  next.resize((size_t)3 * nn);
+  rk.resize((size_t)nn);
+  src.resize((size_t)4 * nn);
   for (long j = 0; j < nn; ++j) {
     const long i = perm[(size_t)j];
     rk[(size_t)j] = k0[(size_t)i];
+    for (int e = 0; e < 3; ++e) next[(size_t)(3 * j + e)] = nx[(size_t)(3 * i + e)];
     for (int e = 0; e < 4; ++e) src[(size_t)(e * nn + j)] = s0[(size_t)(4 * i + e)];
   }
-  next.swap(nx);
   return DG_OK;
 }
 
