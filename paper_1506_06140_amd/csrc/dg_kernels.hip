@@ -4655,48 +4655,59 @@ namespace {
 constexpr int kTreeBlock = 64;
 unsigned tree_blocks(long n) { return (unsigned)((n + kTreeBlock - 1) / kTreeBlock); }
 
-inline uint64_t tkey(int l, long x, long y) { return ((uint64_t)l << 58) | ((uint64_t)x << 29) | (uint64_t)y; }
-
 constexpr int kTreeInts = 17;  // per leaf: level, 4 face infos, 8 neighbours, 4 group members
 
-// Leaf of a (level, x, y) key: open addressing with linear probes in one array
-// of twice the leaves or more (a node-based map spent most of an adaptation's
-// host time in its lookups and allocations).
+// The leaves as quadtrees over the base cells: a cell's entry is the leaf that
+// it is (>= 0), kNone, or the block of its four children.  A lookup is one
+// short descent, which finds the cell, the coarser leaf that covers it or the
+// finer ones in it alike.  10414 leaves on three levels, us on one host core: tables 2400 with
+// an open-addressing hash map -> 600, side lists 1000 -> 450 (a node-based map,
+// before that, took twice the hash map's time for a whole adaptation).
 struct TreeIndex {
-  struct Slot {
-    uint64_t key;
-    int leaf;
-  };
-  static constexpr uint64_t kFree = ~0ull;  // no key: levels end at 24
-  std::vector<Slot> slot;
-  int shift = 0;
+  static constexpr int kNone = -1;
+  std::vector<int> base, kids;  // [ny][nx]; blocks of four, child x | y << 1
   long nx = 0, ny = 0;
   int bc[2] = {0, 0};
+  size_t most = 0;
+  static int block(int v) { return 4 * (-2 - v); }  // of an entry below kNone
   void init(const dg_ctx *c, long nl) {
-    int bits = 4;
-    while ((1L << bits) < 2 * nl) ++bits;
-    slot.assign((size_t)1 << bits, Slot{kFree, -1});
-    shift = 64 - bits;
     nx = c->nx;
     ny = c->ny;
     bc[0] = c->cfg.bc[0];
     bc[1] = c->cfg.bc[1];
+    base.assign((size_t)(nx * ny), kNone);
+    kids.clear();
+    most = (size_t)(nl + nl / 2);  // a tiling has at most 4/3 of its leaves here
+    kids.reserve(most);
   }
-  // the key's slot, or the free one where it belongs (a mixed product: x and y
-  // of neighbouring leaves spread over the array)
-  size_t at(uint64_t key) const {
-    uint64_t h = key * 0x9e3779b97f4a7c15ull;
-    h ^= h >> 32;
-    size_t i = (size_t)((h * 0x9e3779b97f4a7c15ull) >> shift);
-    while (slot[i].key != key && slot[i].key != kFree) i = (i + 1) & (slot.size() - 1);
-    return i;
-  }
-  // false if the key is there already
-  bool add(uint64_t key, int leaf) {
-    Slot &e = slot[at(key)];
-    if (e.key == key) return false;
-    e = Slot{key, leaf};
+  // false if the cell lies in a leaf or holds one (or the set is no tiling)
+  bool add(int l, long x, long y, int leaf) {
+    size_t at = (size_t)((y >> l) * nx + (x >> l));
+    std::vector<int> *in = &base;
+    for (int d = 1; d <= l; ++d) {
+      int v = (*in)[at];
+      if (v >= 0) return false;
+      if (v == kNone) {
+        if (kids.size() > most) return false;
+        v = -2 - (int)(kids.size() / 4);
+        (*in)[at] = v;
+        kids.insert(kids.end(), 4, kNone);
+      }
+      in = &kids;
+      at = (size_t)(block(v) + (int)(((x >> (l - d)) & 1) | (((y >> (l - d)) & 1) << 1)));
+    }
+    if ((*in)[at] != kNone) return false;
+    (*in)[at] = leaf;
     return true;
+  }
+  // the entry of level-l cell (x, y), or of the leaf that covers it; d: its level
+  int walk(int l, long x, long y, int &d) const {
+    int v = base[(size_t)((y >> l) * nx + (x >> l))];
+    for (d = 0; d < l && v < kNone;) {
+      ++d;
+      v = kids[(size_t)(block(v) + (int)(((x >> (l - d)) & 1) | (((y >> (l - d)) & 1) << 1)))];
+    }
+    return v;
   }
   // level-l cell (x, y) wrapped onto the periodic domain; false outside a wall
   bool wrap(int l, long &x, long &y) const {
@@ -4711,23 +4722,32 @@ struct TreeIndex {
     }
     return true;
   }
-  int find(int l, long x, long y) const {
-    return slot[at(tkey(l, x, y))].leaf;
-  }
   // the leaf that covers level-l cell (x, y) if it is that cell or coarser, else -1
   int covering(int l, long x, long y) const {
-    for (int q = l; q >= 0; --q) {
-      const int j = find(q, x >> (l - q), y >> (l - q));
-      if (j >= 0) return j;
+    int d;
+    const int v = walk(l, x, y, d);
+    return v >= 0 ? v : -1;
+  }
+  // the leaves of level-l cell (x, y)'s sibling group, in child order; false
+  // unless all four are leaves
+  bool group(int l, long x, long y, int (&g)[4]) const {
+    if (l < 1) return false;
+    int d;
+    const int v = walk(l - 1, x >> 1, y >> 1, d);
+    if (v >= kNone) return false;
+    bool all = true;
+    for (int ch = 0; ch < 4; ++ch) {
+      g[ch] = kids[(size_t)(block(v) + ch)];
+      all &= g[ch] >= 0;
     }
-    return -1;
+    return all;
   }
 };
 
 // Validates a leaf set (a tiling of the base grid) and indexes it.
 int tree_index(const dg_ctx *c, const std::vector<int32_t> &lv, TreeIndex &ix) {
   const long nl = (long)lv.size() / 3;
-  if (nl < 1 || nl > (1L << 30)) return DG_EINVAL;
+  if (nl < 1 || nl > (1L << 30) || nl / c->nx < c->ny) return DG_EINVAL;  // a base cell has a leaf or more
   ix.init(c, nl);
   int L = 0;
   for (long i = 0; i < nl; ++i) {
@@ -4735,30 +4755,13 @@ int tree_index(const dg_ctx *c, const std::vector<int32_t> &lv, TreeIndex &ix) {
     const long x = lv[3 * i + 1], y = lv[3 * i + 2];
     if (l < 0 || l > 24 || (c->nx << l) >= (1L << 29) || (c->ny << l) >= (1L << 29)) return DG_EINVAL;
     if (x < 0 || y < 0 || x >= (c->nx << l) || y >= (c->ny << l)) return DG_EINVAL;
-    if (!ix.add(tkey(l, x, y), (int)i)) return DG_EINVAL;
+    if (!ix.add(l, x, y, (int)i)) return DG_EINVAL;  // no leaf in another
     L = l > L ? l : L;
   }
   unsigned __int128 area = 0;
-  for (long i = 0; i < nl; ++i) {
-    const int l = lv[3 * i];
-    for (int q = 0; q < l; ++q)  // no leaf inside another
-      if (ix.find(q, lv[3 * i + 1] >> (l - q), lv[3 * i + 2] >> (l - q)) >= 0) return DG_EINVAL;
-    area += (unsigned __int128)1 << (2 * (L - l));
-  }
+  for (long i = 0; i < nl; ++i) area += (unsigned __int128)1 << (2 * (L - lv[3 * i]));
   if (area != ((unsigned __int128)(c->nx * c->ny) << (2 * L))) return DG_EINVAL;
   return DG_OK;
-}
-
-// the leaves of the sibling group of level-l cell (x, y), in child order;
-// false unless all four are there
-bool tree_group(const TreeIndex &ix, int l, long x, long y, int (&g)[4]) {
-  if (l < 1) return false;
-  bool all = true;
-  for (int ch = 0; ch < 4 && all; ++ch) {
-    g[ch] = ix.find(l, 2 * (x >> 1) + (ch & 1), 2 * (y >> 1) + (ch >> 1));
-    all = g[ch] >= 0;
-  }
-  return all;
 }
 
 // Validates a leaf set (a tiling, the level jump across every face at most
@@ -4780,28 +4783,37 @@ int tree_tables(const dg_ctx *c, const std::vector<int32_t> &lv, TreeIndex &ix, 
       int kind, sub = 0, n0 = -1, n1 = -1;
       if (!ix.wrap(l, X, Y)) {
         kind = 1;
-      } else if ((n0 = ix.find(l, X, Y)) >= 0) {
-        kind = 0;
-      } else if (l > 0 && (n0 = ix.find(l - 1, X >> 1, Y >> 1)) >= 0) {
-        kind = 3;
-        sub = (int)((a == 0 ? y : x) & 1);
-        // the child of the coarse leaf that the same-level cell (X, Y) is (limiters)
-        sub |= (int)(((X & 1) | ((Y & 1) << 1)) << 1);
       } else {
-        kind = 2;
-        // the two children of the same-level neighbour that touch this face
-        const long cx = 2 * X + (a == 0 ? (s ? 0 : 1) : 0), cy = 2 * Y + (a == 1 ? (s ? 0 : 1) : 0);
-        n0 = ix.find(l + 1, cx, cy);
-        n1 = ix.find(l + 1, cx + (a == 0 ? 0 : 1), cy + (a == 0 ? 1 : 0));
-        if (n0 < 0 || n1 < 0) return DG_EINVAL;  // a level jump above one
+        int d;
+        const int v = ix.walk(l, X, Y, d);
+        if (v >= 0 && d == l) {
+          kind = 0;
+          n0 = v;
+        } else if (v >= 0 && d == l - 1) {
+          kind = 3;
+          n0 = v;
+          sub = (int)((a == 0 ? y : x) & 1);
+          // the child of the coarse leaf that the same-level cell (X, Y) is (limiters)
+          sub |= (int)(((X & 1) | ((Y & 1) << 1)) << 1);
+        } else if (v < TreeIndex::kNone) {
+          kind = 2;
+          // the two children of the same-level neighbour that touch this face
+          const int *ch = ix.kids.data() + TreeIndex::block(v), near = s ? 0 : 1;
+          n0 = a == 0 ? ch[near] : ch[2 * near];
+          n1 = a == 0 ? ch[near + 2] : ch[2 * near + 1];
+          if (n0 < 0 || n1 < 0) return DG_EINVAL;  // a level jump above one
+        } else {
+          return DG_EINVAL;
+        }
       }
       info[(long)side * nl + i] = kind | (sub << 2);
       nb[(long)(2 * side) * nl + i] = n0;
       nb[(long)(2 * side + 1) * nl + i] = n1;
     }
     int g[4];
-    if (tree_group(ix, l, x, y, g))
-      for (int ch = 0; ch < 4; ++ch) grp[(long)ch * nl + i] = g[ch];
+    if (!((x | y) & 1) && ix.group(l, x, y, g))  // once, from child 0
+      for (int m : g)
+        for (int ch = 0; ch < 4; ++ch) grp[(long)ch * nl + m] = g[ch];
   }
   return DG_OK;
 }
@@ -4864,11 +4876,7 @@ int tree_upload(dg_ctx *c, std::vector<int32_t> &lv, TreeIndex &ix, const std::v
   std::vector<int> R((size_t)8 * nl, 0), in;
   R.reserve((size_t)10 * nl);
   const int *info = T.data() + nl;
-  struct Cell {
-    int l;
-    long x, y;
-  };
-  Cell todo[4 * 25];  // a level adds at most three to the stack
+  int todo[4 * 25];  // a level adds at most three to the stack
   for (long i = 0; i < nl; ++i)
     for (int side = 0; side < 4; ++side) {
       if ((info[(long)side * nl + i] & 3) != 2) continue;
@@ -4876,17 +4884,16 @@ int tree_upload(dg_ctx *c, std::vector<int32_t> &lv, TreeIndex &ix, const std::v
       long X = lv[3 * i + 1] + (a == 0 ? (sd ? 1 : -1) : 0), Y = lv[3 * i + 2] + (a == 1 ? (sd ? 1 : -1) : 0);
       ix.wrap(l, X, Y);
       in.clear();
-      int n = 0;
-      todo[n++] = {l, X, Y};
+      int n = 0, d;
+      todo[n++] = ix.walk(l, X, Y, d);
       while (n > 0) {
-        const Cell e = todo[--n];
-        const int j = ix.find(e.l, e.x, e.y);
-        if (j >= 0) {
-          in.push_back(j);
+        const int v = todo[--n];
+        if (v >= 0) {
+          in.push_back(v);
           continue;
         }
-        if (e.l >= 24) return DG_EINVAL;
-        for (int ch = 0; ch < 4; ++ch) todo[n++] = {e.l + 1, 2 * e.x + (ch & 1), 2 * e.y + (ch >> 1)};
+        if (v == TreeIndex::kNone) return DG_EINVAL;
+        for (int ch = 0; ch < 4; ++ch) todo[n++] = ix.kids[(size_t)(TreeIndex::block(v) + ch)];
       }
       std::sort(in.begin(), in.end());
       R[(size_t)(side * nl + i)] = (int)(R.size() - 8 * nl);
@@ -5006,7 +5013,7 @@ int tree_plan(const dg_ctx *c, const std::vector<int> &flags, int max_level, std
   for (long i = 0; i < nl; ++i) {
     if (!(flags[(size_t)i] & 4) || (flags[(size_t)i] & 2) || L(i) < 1) continue;
     int grp[4];
-    if ((X(i) & 1) || (Y(i) & 1) || !tree_group(ix, L(i), X(i), Y(i), grp)) continue;  // the group's child 0 decides
+    if ((X(i) & 1) || (Y(i) & 1) || !ix.group(L(i), X(i), Y(i), grp)) continue;  // the group's child 0 decides
     bool ok = true;
     for (int ch = 0; ch < 4 && ok; ++ch) {
       const long m = grp[ch];
@@ -5036,7 +5043,7 @@ int tree_plan(const dg_ctx *c, const std::vector<int> &flags, int max_level, std
       }
     } else if (merge[(size_t)i]) {
       int grp[4];
-      if (!tree_group(ix, L(i), X(i), Y(i), grp) || grp[0] != i) continue;
+      if (!ix.group(L(i), X(i), Y(i), grp) || grp[0] != i) continue;
       nx.insert(nx.end(), {L(i) - 1, (int32_t)(X(i) >> 1), (int32_t)(Y(i) >> 1)});
       k0.push_back(2);
       s0.insert(s0.end(), {grp[0], grp[1], grp[2], grp[3]});
