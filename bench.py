@@ -52,7 +52,8 @@ FP64_PEAK_TFLOPS = 78.6
 FP32_PEAK_TFLOPS = 157.3
 METRIC = "DOF-updates/s per RK stage"
 CSRC = os.path.join(ROOT, "paper_1506_06140_amd", "csrc")
-KERNEL_SRC = ("dg_device.h", "dg_line.h", "dg_march3d.hip", "dg_kernels.hip")
+KERNEL_SRC = ("dg_device.h", "dg_line.h", "dg_march.h", "dg_march3d.hip", "dg_split3d.hip", "dg_split2d.hip",
+              "dg_kernels.hip")
 PROFILES = os.path.join(ROOT, "profiles")
 
 # source regions whose text fingerprints a kernel (a counter summary taken on
@@ -64,19 +65,24 @@ _HELPERS = [
     ("// HLLC numerical flux in +a between traces UL (low side) and UR (high side),",
      "// One stage of the time integrator in Shu-Osher form (App. D): with u the"),
 ]
+# one-dimensional blocks, the line Riemann solver, buffers and face contractions
+_LINE = [("// One-dimensional building blocks of the sum-factorised stage kernels: the",
+          "// Planes per wave: all waves run alike, one (k = 2) or two (k = 1) per SIMD at")]
+
 KERNELS = {
     "stage3d": dict(name="k_rhs_march3d<2>", traffic="k_rhs_march3d_kh3d128_k2_traffic.txt",
-                    regions=[("// One-dimensional building blocks of the sum-factorised stage kernels: the",
-                              "// Planes per wave: all waves run alike, one (k = 2) or two (k = 1) per SIMD at")]),
-    "stage3d_amr": dict(name="k_rhs_mfma3d<3,AMR>", traffic="k_rhs_mfma3d_blast64box_k3_traffic.txt",
-                        regions=_HELPERS + [("// 3D right-hand side + stage with the contractions on MFMA (FP64; FP32 and",
-                                             "// Discrete adjoint of the right-hand side and of the SSP-RK3 stages.")]),
+                    regions=_LINE + [("// 3D right-hand side + stage, one thread per cell, sum-factorised (FP64).",
+                                      "// FP64 on uniform 3D grids at k = 1 and 2 without gravity, states below 4 GB")]),
+    "stage3d_amr": dict(name="k_rhs_split3d<3,AMR> + k_box_faces<3>",
+                        traffic="k_rhs_split3d_blast64box_k3_traffic.txt",
+                        regions=_LINE + [("// 3D right-hand side + stage, the work of 63 cells split over four waves",
+                                          "// FP64 in 3D without gravity, states below 4 GB")]),
     "stage3d_valu": dict(name="k_rhs_stage<3,2,double>", traffic="k_rhs_stage_kh3d128_k2_traffic.txt",
                          regions=_HELPERS + [("// Right-hand side and fused stage.",
                                               "// 2D right-hand side + SSP-RK3 stage on LDS tiles, four lanes per cell.")]),
-    "tile2d": dict(name="k_rhs_tile2d<2,double> (8x8 tiles)", traffic="k_rhs_tile2d_vortex256_k2_traffic.txt",
-                   regions=_HELPERS + [("// 2D right-hand side + SSP-RK3 stage on LDS tiles, four lanes per cell.",
-                                        "// 3D right-hand side + stage with the contractions on MFMA (FP64; FP32 and")]),
+    "split2d": dict(name="k_rhs_split2d<2>", traffic="k_rhs_split2d_vortex256_k2_traffic.txt",
+                    regions=_LINE + [("// 2D right-hand side + stage, a cell's work split over four waves (FP64).",
+                                      "// FP64 on 2D grids without a refined box or a tree, unless")]),
 }
 
 
@@ -388,11 +394,11 @@ def variants():
     # fused RHS + stage launch, HIP events), with the limiter pass
     kinds = {
         "kh3d": ("3D shear layer 128^3, k=2", {},
-                 {"fp64_mfma": "k_rhs_march3d<2>", "fp64_valu": "k_rhs_stage<3,2,double>",
+                 {"fp64": "k_rhs_march3d<2>", "fp64_valu": "k_rhs_stage<3,2,double>",
                   "fp32_valu": "k_rhs_stage<3,2,float>", "fp32_mfma": None,
                   "bf16_mfma": "k_rhs_mfma3d<2,float,BF16 volume>"}),
         "blast_amr": ("3D blast, 64^3 base grid + refined 32^3 box (64^3 fine cells), k=3", {"eps": 1e-4},
-                      {"fp64_mfma": "k_rhs_mfma3d<3,AMR>", "fp64_valu": "k_rhs_amr_quad<3>",
+                      {"fp64": "k_rhs_split3d<3,AMR> + k_box_faces<3>", "fp64_valu": "k_rhs_amr_quad<3>",
                        "fp32_valu": "k_rhs_amr<3,3,float>", "fp32_mfma": "k_rhs_mfma3d<3,AMR,float>",
                        "bf16_mfma": "k_rhs_mfma3d<3,AMR,float,BF16 volume>"}),
     }
@@ -402,7 +408,7 @@ def variants():
         for label, kname in kernels.items():
             if kname is None:
                 continue  # FP32 on a uniform k = 2 grid has no MFMA form (the VALU kernel is faster)
-            prec, path = label.split("_")
+            prec, path = (label + "_").split("_")[:2]
             s = dg.Solver(dict(wl, path3d=dg.DG_PATH3D_VALU if path == "valu" else dg.DG_PATH3D_AUTO), prec)
             w = build_state(s, wl)
             s.limit(w)
@@ -413,7 +419,7 @@ def variants():
             peak = FP64_PEAK_TFLOPS if prec == "fp64" else FP32_PEAK_TFLOPS
             rec["kernels"][label] = {"kernel": kname, "ms": kms, "alu_frac": f3 * cells / (kms * 1e-3) / 1e12 / peak,
                                      "alu_peak_tflops": peak}
-            if label == "fp64_mfma":
+            if label == "fp64":
                 rec["limiter_ms"] = kernel_ms(s, w, bufs, 10, limiter=True)
                 rec["cells"] = cells
                 rec["alg_flops_per_launch"] = f3 * cells
@@ -639,8 +645,8 @@ def vortex2d_line(steps=400, warmup=20, with_cpu=True, reps=300, n=256, k=2, pre
                        "CFL 0.2, no limiter, seeded 1e-3 density noise",
            "ms_per_step": ms, "dof_updates_per_s": s.ncell * s.N * 3 / (ms * 1e-3),
            "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                        "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic("tile2d") if base else None,
-                        "kernel": f"k_rhs_tile2d<{k},{'double' if precision == 'fp64' else 'float'}>",
+                        "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic("split2d") if base else None,
+                        "kernel": f"k_rhs_split2d<{k}>" if precision == "fp64" else f"k_rhs_tile2d<{k},float>",
                         "kernel_ms": kms, "alg_bytes_per_launch": alg_bytes,
                         "fp64_frac": f * s.ncell / (kms * 1e-3) / 1e12 / FP64_PEAK_TFLOPS}}
     if with_cpu:
@@ -719,6 +725,8 @@ def main():
                                ("3D Sod-type blast, 64^3 base grid + refined central 32^3 base cells (64^3 fine "
                                 "cells), k=3 (N=20), FP64, SSP-RK3, CFL 0.2, minmod + positivity limiter"),
                    "cells": cells, "dof": dof, "stages_per_step": 3, "graph": bool(args.graph)},
+        # "mfma": the FP64 datapath, which matrix and vector instructions share;
+        # alg_flops counts the contractions as dense products (alg_work)
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / FP64_PEAK_TFLOPS, "traffic": measured_traffic(kname),
                      "kernel": KERNELS[kname]["name"], "kernel_ms": k_ms,

@@ -625,7 +625,6 @@ struct TreeGrid {
   double fac0;      // (2/dx) 2^-d of level 0
   double dx0;
   double gamma;
-  const double *t1; // 1D tables (tables_1d)
 };
 
 // Stage kernels of the other source files.  launch_line runs the stage on one

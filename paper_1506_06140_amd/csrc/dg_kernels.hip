@@ -4343,13 +4343,6 @@ int dg_init(const dg_config *cfg, dg_ctx **out) {
     if ((e = hipMalloc((void **)&c->prmat, P.size() * sizeof(double))) != hipSuccess) return fail(e);
     if ((e = hipMemcpy(c->prmat, P.data(), P.size() * sizeof(double), hipMemcpyHostToDevice)) != hipSuccess)
       return fail(e);
-    if (cfg->dim == 2) {
-      // 1D tables of the quadtree stage kernel
-      const std::vector<double> t1 = dg::tables_1d(cfg->k);
-      if ((e = hipMalloc((void **)&c->t1d, t1.size() * sizeof(double))) != hipSuccess) return fail(e);
-      if ((e = hipMemcpy(c->t1d, t1.data(), t1.size() * sizeof(double), hipMemcpyHostToDevice)) != hipSuccess)
-        return fail(e);
-    }
   }
   *out = c;
   return DG_OK;
@@ -4376,7 +4369,6 @@ void dg_destroy(dg_ctx *c) {
   if (c->tflags) (void)hipFree(c->tflags);
   if (c->treg) (void)hipFree(c->treg);
   if (c->tplist) (void)hipFree(c->tplist);
-  if (c->t1d) (void)hipFree(c->t1d);
   if (c->tnbm) (void)hipFree(c->tnbm);
   delete c;
 }
@@ -4828,7 +4820,6 @@ dg::TreeGrid make_tree_grid(const dg_ctx *c) {
   g.fac0 = 2.0 / c->dx / 4.0;
   g.dx0 = c->dx;
   g.gamma = c->cfg.gamma;
-  g.t1 = c->t1d;
   return g;
 }
 

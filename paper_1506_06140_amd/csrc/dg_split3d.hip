@@ -6,7 +6,7 @@ namespace dg {
 
 // One Cartesian block of cells: the grid, or the coarse or the fine block of
 // a refined box.
-struct SplitPart {
+struct Split3Part {
   int n[3];
   int wall[3];
   double fac;        // (2/dx) 2^-d
@@ -15,8 +15,8 @@ struct SplitPart {
   long columns;      // (nx + 1) ny
   long planes;       // blocks of 63 columns, times nz
 };
-struct SplitGrid {
-  SplitPart p[2];
+struct Split3Grid {
+  Split3Part p[2];
   int lo[3], hi[3];  // base cells under the fine block
   long total;        // planes of both parts
   long doubles;      // the whole state
@@ -322,7 +322,7 @@ constexpr long kGroups = 256;  // workgroups of a launch: one per compute unit (
 
 template <int K, int FX, bool AMR>
 __global__ __launch_bounds__(256, 1) void k_rhs_split3d(const double *__restrict__ w, double *__restrict__ out,
-                                                        const double *__restrict__ dtp, SplitGrid g, int mode, Mix mx,
+                                                        const double *__restrict__ dtp, Split3Grid g, int mode, Mix mx,
                                                         int *__restrict__ flag) {
   constexpr int N = (K + 1) * (K + 2) * (K + 3) / 6, N2 = (K + 1) * (K + 2) / 2, n1 = K + 1;
   constexpr int NP = K * (K + 1) / 2, NO = (5 * N + 3) / 4;
@@ -368,7 +368,7 @@ __global__ __launch_bounds__(256, 1) void k_rhs_split3d(const double *__restrict
   // the cell at (x, y, zz) of part P, at most one index one past its range: a
   // periodic or wall neighbour, or (fine block) the coarse cell beside it
   // (the box keeps a cell's distance from the domain's faces)
-  auto ref = [&](const SplitPart &P, bool fine, int x, int y, int zz) __attribute__((always_inline)) {
+  auto ref = [&](const Split3Part &P, bool fine, int x, int y, int zz) __attribute__((always_inline)) {
     CellRef r;
     r.i[0] = x;
     r.i[1] = y;
@@ -407,7 +407,7 @@ __global__ __launch_bounds__(256, 1) void k_rhs_split3d(const double *__restrict
 #pragma unroll 1
   for (long p = p0; p < p1; ++p) {
     const bool fine = AMR && p >= g.p[0].planes;
-    const SplitPart &P = g.p[fine ? 1 : 0];
+    const Split3Part &P = g.p[fine ? 1 : 0];
     const long q = fine ? p - g.p[0].planes : p;
     const int nx = P.n[0], ny = P.n[1], nz = P.n[2];
     const int cb = (int)(q / nz), z = (int)(q % nz);
@@ -652,7 +652,7 @@ __global__ __launch_bounds__(256, 1) void k_rhs_split3d(const double *__restrict
 // additions is fixed.
 template <int K, int FX>
 __global__ __launch_bounds__(64, 1) void k_box_faces(const double *__restrict__ w, double *__restrict__ out,
-                                                     const double *__restrict__ dtp, SplitGrid g, int mode, double cl,
+                                                     const double *__restrict__ dtp, Split3Grid g, int mode, double cl,
                                                      int *__restrict__ flag) {
   constexpr int N = (K + 1) * (K + 2) * (K + 3) / 6, N2 = (K + 1) * (K + 2) / 2;
   __shared__ double sx[5 * N2 * 64];
@@ -671,8 +671,8 @@ __global__ __launch_bounds__(64, 1) void k_box_faces(const double *__restrict__ 
   const int face = 16 * blk + (lane >> 2), f = min(face, n1 * n2 - 1), b1 = lane & 1, b2 = (lane >> 1) & 1;
   const bool real = face < n1 * n2 && (lane & 3) == 0;
   const int j1 = f % n1, j2 = f / n1;
-  const SplitPart &C = g.p[0], &F = g.p[1];
-  auto cell_of = [&](const SplitPart &P, int a, int x1, int x2) {
+  const Split3Part &C = g.p[0], &F = g.p[1];
+  auto cell_of = [&](const Split3Part &P, int a, int x1, int x2) {
     const int x = axis == 0 ? a : x1, y = axis == 1 ? a : axis == 0 ? x1 : x2, z = axis == 2 ? a : x2;
     return 8u * ((unsigned)P.base + ((unsigned)z * (unsigned)P.n[1] + (unsigned)y) * (unsigned)P.n[0] + (unsigned)x);
   };
@@ -769,11 +769,11 @@ bool dg::split3d_takes(const dg_ctx *c) {
 
 int dg::launch_split3d(const dg_ctx *c, const double *w, double *out, const double *dt, int mode, const Mix &mx,
                        hipStream_t s) {
-  SplitGrid g;
+  Split3Grid g;
   const int n[3] = {(int)c->nx, (int)c->ny, (int)c->nz};
   g.total = 0;
   for (int i = 0; i < 2; ++i) {
-    SplitPart &p = g.p[i];
+    Split3Part &p = g.p[i];
     for (int a = 0; a < 3; ++a) {
       p.n[a] = i == 0 ? n[a] : c->amr ? (int)c->nf[a] : 1;
       p.wall[a] = i == 0 && c->cfg.bc[a] == DG_BC_TRANSMISSIVE;
