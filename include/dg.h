@@ -105,15 +105,16 @@ typedef struct {
                       /* DG_TILE2D_LARGE (16 x 16 for k <= 2, 16 x 8 for k =   */
                       /* 3, 4): tiles of that shape; results equal to rounding */
   int path3d;         /* 3D, no gravity: DG_PATH3D_AUTO (0) runs FP64 on       */
-                      /* uniform grids at k = 1 and 2 on the sum-factorised    */
-                      /* kernel (k = 2 on grids of up to 16384 cells and       */
-                      /* states of 4 GB or more excepted), and otherwise at    */
-                      /* k = 2 or 3 the stage kernel's contractions on MFMA:   */
-                      /* FP64 on FP64 MFMA; FP32 on FP32 MFMA at k = 3 and on  */
+                      /* sum-factorised kernels (uniform grids; the refined    */
+                      /* box at k = 2, 3), except k = 2 on up to 16384 cells,  */
+                      /* k = 3 on as many in narrow rows and states of 4 GB or */
+                      /* more: these, at k = 2 and 3, have the contractions on */
+                      /* FP64 MFMA; FP32 on FP32 MFMA at k = 3 and on          */
                       /* refined boxes (FP32 at k = 2 on a uniform grid keeps  */
                       /* the one-thread-per-cell kernel, faster there);        */
-                      /* DG_PATH3D_VALU runs them on the vector ALU (one       */
-                      /* thread per cell; FP64 at k = 3 four lanes per cell);  */
+                      /* DG_PATH3D_VALU runs the dense contractions on the     */
+                      /* vector ALU (one thread per cell; FP64 at k = 3 four   */
+                      /* lanes per cell);                                      */
                       /* results equal to rounding                             */
 } dg_config;
 
