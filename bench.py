@@ -575,7 +575,7 @@ def tree_variant(max_level: int = 5, steps: int = 100, reps: int = 30):
            "refined_leaf_fraction": float((lv > 0).mean()), "refined_area_fraction": float(area[lv > 0].sum() / area.sum()),
            "uniform_equivalent_cells": (n << max_level) ** 2,
            "ms_per_step": ms, "dof_updates_per_s": cells * s.N * 3 / (ms * 1e-3),
-           "adapt_ms": t_adapt * 1e3, "stage_kernel": "k_rhs_tree<3,0>", "stage_kernel_ms": kms,
+           "adapt_ms": t_adapt * 1e3, "stage_kernel": "k_rhs_split_tree<3,0>", "stage_kernel_ms": kms,
            "stage_kernel_alu_frac": f3 * cells / (kms * 1e-3) / 1e12 / FP64_PEAK_TFLOPS, "status": st}
     del s, A, B, bufs
     torch.cuda.empty_cache()
