@@ -29,8 +29,7 @@ struct Cfg {
   static constexpr int XQ = PS + NS * N;
   static constexpr int HG = XQ + 3 * Q;
   static constexpr int HW = HG + D * 2 * 4 * QF * N;
-  static constexpr int CM = HW + D * 2 * 4 * QF * N;
-  static constexpr int TOTAL = CM + 8 * N;
+  static constexpr int TOTAL = HW + D * 2 * 4 * QF * N;
 };
 
 struct Grid {

@@ -35,9 +35,8 @@ Shape make_shape(int d, int k);
 //   HG [d][2][4][QF][N] coarse basis at the nodes of the 2^(d-1) fine faces
 //                    covering a coarse face (static 2:1 refinement)
 //   HW [d][2][4][QF][N] HG times the fine-face weight / 2^(d-1) (coarse lift)
-//   CM [8][N]        mean of phi_l over each child subcell
 struct Layout {
-  int B, DW, TF, TW, WQ, PS, XQ, HG, HW, CM, total;
+  int B, DW, TF, TW, WQ, PS, XQ, HG, HW, total;
 };
 
 Layout make_layout(const Shape &s);

@@ -3501,7 +3501,7 @@ struct LayoutCheck {
     using C = Cfg<D, K>;
     const dg::Layout &l = c->lay;
     bool ok = l.B == C::B && l.DW == C::DW && l.TF == C::TF && l.TW == C::TW && l.WQ == C::WQ &&
-              l.PS == C::PS && l.XQ == C::XQ && l.HG == C::HG && l.HW == C::HW && l.CM == C::CM && l.total == C::TOTAL &&
+              l.PS == C::PS && l.XQ == C::XQ && l.HG == C::HG && l.HW == C::HW && l.total == C::TOTAL &&
               c->sh.N == C::N && c->sh.NS == C::NS;
     return ok ? DG_OK : DG_EINVAL;
   }

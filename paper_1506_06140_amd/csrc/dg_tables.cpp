@@ -131,7 +131,6 @@ Layout make_layout(const Shape &s) {
   L.XQ = o; o += 3 * s.Q;
   L.HG = o; o += s.d * 2 * 4 * s.QF * s.N;
   L.HW = o; o += s.d * 2 * 4 * s.QF * s.N;
-  L.CM = o; o += 8 * s.N;
   L.total = o;
   return L;
 }
@@ -236,21 +235,6 @@ std::vector<double> build_tables(const Shape &s, double *gll_w1) {
           }
         }
   }
-  // child means: 2^-d sum_q w_q phi_l((xi_q + c)/2) (exact: degree <= k)
-  for (int ch = 0; ch < (1 << s.d); ++ch)
-    for (int l = 0; l < s.N; ++l) {
-      double acc = 0.0;
-      for (int q = 0; q < s.Q; ++q) {
-        int idx[3] = {q % s.n1, (q / s.n1) % s.n1, q / (s.n1 * s.n1)};
-        double xi[3] = {0.0, 0.0, 0.0}, wq = 1.0;
-        for (int a = 0; a < s.d; ++a) {
-          xi[a] = 0.5 * (gx[idx[a]] + (((ch >> a) & 1) ? 1.0 : -1.0));
-          wq *= gw[idx[a]];
-        }
-        acc += basis(l, xi) * wq;
-      }
-      t[L.CM + ch * s.N + l] = acc / (double)(1 << s.d);
-    }
   return t;
 }
 
