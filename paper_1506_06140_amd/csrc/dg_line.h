@@ -192,8 +192,9 @@ __device__ __forceinline__ double rsq3(double x) {
 // S* / (S_K - S*) where 0 lies between S_K and S*, else the side's own
 // momentum m_K, not rounded again (rho_K u_K instead made a cold supersonic
 // disc's right-hand side 1.3 to 1.7 times as far from exact).  A trace without
-// a real sound speed gives NaN as in hllc (0 (c_L + c_R) is added to S*: the
-// hardware's min and max drop a NaN operand).
+// a real sound speed gives NaN in every flux as in hllc (0 (c_L + c_R) is added
+// to S*: the hardware's min and max drop a NaN operand; and S* enters f with
+// the factor 0 where f is m_K).
 template <int D, int A, int FX>
 __device__ __forceinline__ void hllc_line(const double (&UL)[D + 2], const double (&UR)[D + 2], double g, double (&F)[D + 2]) {
 #pragma clang fp contract(off)
@@ -242,8 +243,8 @@ __device__ __forceinline__ void hllc_line(const double (&UL)[D + 2], const doubl
   const double e = left ? eL : eR, mK = left ? UL[1 + A] : UR[1 + A];
   const double iv = rcp3(S - Ss);
   const bool star = left ? S < 0.0 : S > 0.0;  // 0 between S_K and S*
-  const double B = star ? S * iv : 0.0;
-  const double f = star ? rd * (Ss * iv) : mK;
+  const double ik = star ? iv : 0.0, B = S * ik;
+  const double f = fma(rd * ik, Ss, star ? 0.0 : mK);
   const double Aq = B * rd, q = Ss - u;
   F[0] = f;
 #pragma unroll

@@ -1,0 +1,122 @@
+"""GPU: a cell whose trace has no real sound speed (negative pressure) makes
+every flux through its faces NaN, whichever side of the face it is on and
+however the flow runs, the mass flux too, and raises the context's flag: the
+density's tendency is NaN in that cell and in its face neighbours (of the
+refined box and the quadtree also across a level) and finite elsewhere."""
+import numpy as np
+import pytest
+
+import workloads
+from test_gpu_upwind_flux import supersonic
+
+pytestmark = pytest.mark.gpu
+
+CASES = [(2, 1, (64, 5, 1)), (2, 2, (33, 17, 1)), (2, 3, (63, 4, 1)), (2, 4, (17, 9, 1)),
+         (3, 1, (62, 5, 7)), (3, 2, (26, 26, 25)), (3, 3, (64, 3, 4))]
+
+
+def _spoil(w, dim, cell):
+    """Negative pressure in one cell: its energy below its kinetic energy."""
+    w[(dim + 1, 0) + cell] = 0.25 * sum(w[(1 + a, 0) + cell] ** 2 for a in range(dim)) / w[(0, 0) + cell]
+
+
+@pytest.mark.parametrize("flux", [0, 1])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+@pytest.mark.parametrize("dim,k,n", CASES)
+def test_bad_trace_spoils_every_flux(dim, k, n, sign, flux):
+    import torch
+    import paper_1506_06140_amd as dg
+    print("nan flux", dim, k, n, sign, flux, flush=True)
+    wl = workloads.workload("kh3d" if dim == 3 else "density_wave", dim=dim, k=k, n=n, flux=flux, limiter=0,
+                            positivity=0, rk="rk3", length=tuple(m / 64 for m in n))
+    s = dg.Solver(wl)
+    w = supersonic(s.shape, dim, sign, 7)
+    at = (n[2] // 2, n[1] // 2, 3)
+    _spoil(w, dim, at)
+    want = np.zeros(s.shape[2:], dtype=bool)
+    want[at] = True
+    for a in range(dim):
+        for d in (-1, 1):
+            j = list(at)
+            j[2 - a] = (j[2 - a] + d) % n[a]
+            want[tuple(j)] = True
+    L = s.rhs(torch.from_numpy(w).cuda()).cpu().numpy()
+    for v in range(dim + 2):
+        assert (np.isnan(L[v, 0]) == want).all(), v
+    assert s.status() != 0
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+@pytest.mark.parametrize("k", [1, 2, 3])
+def test_bad_trace_spoils_every_flux_tree(k, sign):
+    import torch
+    import paper_1506_06140_amd as dg
+    print("nan flux tree", k, sign, flush=True)
+    n = (13, 5)
+    wl = workloads.workload("kh2d", k=k, n=(*n, 1), length=(n[0] / 8, n[1] / 8, 1.0), limiter=0, positivity=0, rk="rk3")
+    leaves = workloads.random_tree(n, 2, 0.4, 11, periodic=(True, True))
+    s = dg.TreeSolver(wl, leaves)
+    lv = np.asarray(leaves, dtype=np.int64)
+    w = supersonic(s.shape, 2, sign, 5)
+    at = len(lv) // 2
+    _spoil(w, 2, (at,))
+    # leaves that share a part of a side, in units of the finest level's cells
+    top = int(lv[:, 0].max())
+    size = 1 << (top - lv[:, 0])
+    x0, y0 = lv[:, 1] * size, lv[:, 2] * size
+    want = np.zeros(len(lv), dtype=bool)
+    for ox in (-(n[0] << top), 0, n[0] << top):
+        for oy in (-(n[1] << top), 0, n[1] << top):
+            ax, ay, h = x0[at] + ox, y0[at] + oy, size[at]
+            inx = (x0 < ax + h) & (x0 + size > ax)
+            iny = (y0 < ay + h) & (y0 + size > ay)
+            want |= inx & (iny | (y0 == ay + h) | (y0 + size == ay))
+            want |= iny & ((x0 == ax + h) | (x0 + size == ax))
+    L = s.rhs(torch.from_numpy(w).cuda()).cpu().numpy()
+    for v in range(4):
+        assert (np.isnan(L[v, 0]) == want).all(), v
+    assert s.status() != 0
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+@pytest.mark.parametrize("fine", [False, True])
+@pytest.mark.parametrize("k", [2, 3])
+def test_bad_trace_spoils_every_flux_box(k, fine, sign):
+    import torch
+    import paper_1506_06140_amd as dg
+    print("nan flux box", k, fine, sign, flush=True)
+    n, lo, hi = (7, 6, 5), (2, 2, 1), (5, 4, 4)
+    wl = workloads.workload("blast_amr", dim=3, k=k, n=n, refine_lo=lo, refine_hi=hi, limiter=0, positivity=0, rk="rk3",
+                            length=tuple(m / 8.0 for m in n))
+    s = dg.Solver(wl)
+    nc, nf = n[::-1], s.nf[::-1]
+    parts = [supersonic((5, s.N, *nc), 3, sign, 3), supersonic((5, s.N, *nf), 3, sign, 4)]
+    at = (2, 2, 0) if fine else (2, 2, 1)  # [z][y][x]: a fine cell at the box's low x side, the coarse cell beside that side
+    _spoil(parts[1 if fine else 0], 3, at)
+    want = [np.zeros(nc, dtype=bool), np.zeros(nf, dtype=bool)]
+    want[1 if fine else 0][at] = True
+    for a in range(3):
+        for d in (-1, 1):
+            j = list(at)
+            j[2 - a] += d
+            if fine:
+                if 0 <= j[2 - a] < s.nf[a]:
+                    want[1][tuple(j)] = True
+                else:
+                    want[0][tuple(lo[2 - i] + (j[i] >> 1) for i in range(3))] = True
+            else:
+                if all(lo[2 - i] <= j[i] < hi[2 - i] for i in range(3)):
+                    assert a == 0 and d == 1
+                    z, y = 2 * (at[0] - lo[2]), 2 * (at[1] - lo[1])
+                    want[1][z:z + 2, y:y + 2, 0] = True
+                else:
+                    want[0][tuple(j[i] % nc[i] for i in range(3))] = True
+    w = np.concatenate([p.ravel() for p in parts])
+    L = s.rhs(torch.from_numpy(w).cuda()).cpu().numpy()
+    m = 5 * s.N * int(np.prod(nc))
+    hole = np.zeros(nc, dtype=bool)
+    hole[lo[2]:hi[2], lo[1]:hi[1], lo[0]:hi[0]] = True
+    for part, got in ((0, L[:m].reshape(5, s.N, *nc)), (1, L[m:].reshape(5, s.N, *nf))):
+        for v in range(5):
+            assert (np.isnan(got[v, 0]) == want[part])[~hole if part == 0 else ...].all(), (part, v)
+    assert s.status() != 0
