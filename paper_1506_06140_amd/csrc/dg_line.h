@@ -318,8 +318,8 @@ __device__ __forceinline__ void hllc_line_vjp(const double (&UL)[D + 2], const d
   const double S = left ? SL : SR, rho = left ? UL[0] : UR[0], u = left ? uL : uR, p = left ? pL : pR;
   const double e = left ? eL : eR, d = S - u, iv = rcp3(S - Ss), q = Ss - u;
   const bool star = left ? S < 0.0 : S > 0.0;
-  const double B = star ? S * iv : 0.0, rd = rho * d, Aq = B * rd, si = Ss * iv;
-  const double f = rho * (star ? d * si : u);
+  const double ik = star ? iv : 0.0, B = S * ik, rd = left ? aL : aR, Aq = B * rd, si = Ss * iv;
+  const double f = fma(rd * ik, Ss, star ? 0.0 : left ? UL[1 + A] : UR[1 + A]);
 
   // F_0 = f, F_n = u f + p + Aq q, F_t = v_t f, F_E = e f + p u + q (Aq S* + B p)
   double gf = fma(u, G[1 + A], fma(e, G[D + 1], G[0]));
@@ -338,9 +338,8 @@ __device__ __forceinline__ void hllc_line_vjp(const double (&UL)[D + 2], const d
   double gSs = fma(Aq, qE, gq);
   double gu = fma(f, gn, fma(p, gE, -gq));
   const double gB = fma(p, qE, rd * gA);
-  const double h = star ? gf : 0.0, hn = gf - h;  // the star and the plain form of f
-  double grho = fma(B * d, gA, fma(d * si, h, u * hn));
-  gu = fma(rho, hn, gu);
+  const double h = star ? gf : 0.0, hm = gf - h;  // the star form of f, and the momentum as f
+  double grho = fma(B * d, gA, d * si * h);
   const double gd = fma(B * rho, gA, rho * si * h);
   gSs = fma(rd * iv, h, gSs);
   const double giv = fma(rd * Ss, h, star ? S * gB : 0.0);
@@ -423,6 +422,8 @@ __device__ __forceinline__ void hllc_line_vjp(const double (&UL)[D + 2], const d
     GL[1 + b] = fma(irL, gvL[b], -kL * vL[b]);
     GR[1 + b] = fma(irR, gvR[b], -kR * vR[b]);
   }
+  GL[1 + A] += left ? hm : 0.0;
+  GR[1 + A] += left ? 0.0 : hm;
   GL[0] = fma(irL, sL, fma(0.5 * keL * irL, kL, rL));
   GR[0] = fma(irR, sR, fma(0.5 * keR * irR, kR, rR));
 }

@@ -60,3 +60,29 @@ def test_mass_flux_is_the_momentum_tree(k, sign):
     L = s.rhs(torch.from_numpy(w).cuda()).cpu().numpy()
     assert np.abs(L[0, 0]).max() == 0.0
     assert np.abs(L[3, 0]).max() > 0.0 and s.status() == 0
+
+
+@pytest.mark.parametrize("flux", [0, 1])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+@pytest.mark.parametrize("k", [1, 2, 3])
+def test_adjoint_of_the_mass_flux(k, sign, flux):
+    """The reverse sweep of the same faces: the mass flux depends on the upwind
+    cell's momentum alone, with slope one.  A cotangent on the mean density's
+    tendency only then reaches no density and no energy (exactly zero), and a
+    cell's momentum along an axis by 2 fac times the cotangent's difference to
+    the downwind neighbour (k + 1 rounded terms: 8 eps)."""
+    import torch
+    import paper_1506_06140_amd as dg
+    print("upwind adjoint", k, sign, flux, flush=True)
+    n = (33, 17, 1)
+    s = dg.Solver(_grid(2, k, n, flux))
+    w = supersonic(s.shape, 2, sign, 3)
+    lam = np.zeros(s.shape)
+    lam[0, 0] = np.random.default_rng(9).integers(-8, 8, size=s.shape[2:])
+    mu = s.adjoint_rhs(torch.from_numpy(w).cuda(), torch.from_numpy(lam).cuda()).cpu().numpy()
+    assert np.abs(mu[0]).max() == 0.0 and np.abs(mu[3]).max() == 0.0
+    fac = 2.0 * 64 / 4
+    for a in range(2):
+        d = np.roll(lam[0, 0], -1, axis=2 - a) - lam[0, 0] if sign > 0 else lam[0, 0] - np.roll(lam[0, 0], 1, axis=2 - a)
+        assert np.abs(mu[1 + a, 0] - 2.0 * fac * d).max() <= 8 * 2.0 ** -52 * 2.0 * fac * 16
+    assert s.status() == 0
