@@ -67,7 +67,7 @@ _HELPERS = [
 ]
 # one-dimensional blocks, the line Riemann solver, buffers and face contractions
 _LINE = [("// One-dimensional building blocks of the sum-factorised stage kernels: the",
-          "// Planes per wave: all waves run alike, one (k = 2) or two (k = 1) per SIMD at")]
+          "// 3D right-hand side + stage, one thread per cell, sum-factorised (FP64).")]
 
 KERNELS = {
     "stage3d": dict(name="k_rhs_march3d<2>", traffic="k_rhs_march3d_kh3d128_k2_traffic.txt",

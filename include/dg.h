@@ -106,12 +106,13 @@ typedef struct {
                       /* 3, 4): tiles of that shape; results equal to rounding */
   int path3d;         /* 3D, no gravity: DG_PATH3D_AUTO (0) runs FP64 on       */
                       /* sum-factorised kernels (uniform grids; the refined    */
-                      /* box at k = 2, 3), except k = 2 on up to 16384 cells,  */
-                      /* k = 3 on as many in narrow rows and states of 4 GB or */
-                      /* more: these, at k = 2 and 3, have the contractions on */
-                      /* FP64 MFMA; FP32 on FP32 MFMA at k = 3 and on          */
-                      /* refined boxes (FP32 at k = 2 on a uniform grid keeps  */
-                      /* the one-thread-per-cell kernel, faster there);        */
+                      /* box at k = 2, 3), except small grids at k = 2, grids  */
+                      /* and boxes so narrow that they leave those kernels'    */
+                      /* lanes idle, and states of 4 GB or more: these, at     */
+                      /* k = 2 and 3, have the contractions on FP64 MFMA; FP32 */
+                      /* on FP32 MFMA at k = 3 and on refined boxes (FP32 at   */
+                      /* k = 2 on a uniform grid keeps the one-thread-per-cell */
+                      /* kernel, faster there);                                */
                       /* DG_PATH3D_VALU runs the dense contractions on the     */
                       /* vector ALU (one thread per cell; FP64 at k = 3 four   */
                       /* lanes per cell);                                      */

@@ -27,6 +27,7 @@
 
 #include "dg_device.h"
 #include "dg_internal.h"
+#include "dg_rules.h"
 
 // The carried rate's layout as the C ABI states it: the kernels here write it,
 // the binding reads it.
@@ -237,7 +238,6 @@ struct Tile2D<4, 0> { static constexpr int TX = 16, TY = 8; };
 // LDS and more than 256 registers per lane, so a CU runs one wave per SIMD
 // and the 16x8 tiles (two per SIMD) run unless the grid has fewer of them
 // than the GPU has CUs.  force = 0 or 1 overrides the choice.
-constexpr long kCusPerGpu = 256;
 inline bool tile2d_small(int k, long large_tiles, int force) {
   if (force >= 0) return force == 1;
   return k <= 3 || large_tiles < kCusPerGpu;

@@ -183,23 +183,4 @@ __device__ __forceinline__ void face_lift(const double (&m)[(K + 1) * (K + 2) / 
   });
 }
 
-// Planes per wave: all waves run alike, one (k = 2) or two (k = 1) per SIMD at
-// a time, and a wave's cost is about its planes plus a quarter (the first
-// face, the first loads).  128^3, k = 2, us per launch for 4, 7, 8, 12, 16, 32
-// planes: 1366, 1346, 1423, 1330, 1647, 2164; k = 1: 448, 444, 453, 448, 500,
-// 609; 64^3, k = 1, for 1, 3, 6, 12 planes: 87, 79, 85, 150.
-inline int march_len(long columns, int nz, long slots) {
-  double best = 0.0;
-  int at = 1;
-  for (int len = 1; len <= nz && len <= 64; ++len) {
-    const long waves = (columns * ((nz + len - 1) / len) + 61) / 62;
-    const double cost = (double)((waves + slots - 1) / slots) * (len + 0.25);
-    if (len == 1 || cost < best) {
-      best = cost;
-      at = len;
-    }
-  }
-  return at;
-}
-
 }  // namespace dg

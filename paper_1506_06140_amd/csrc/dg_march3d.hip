@@ -1,5 +1,6 @@
 // 3D right-hand side + stage, one thread per cell, sum-factorised (FP64).
 #include "dg_march.h"
+#include "dg_rules.h"
 
 namespace dg {
 
@@ -342,16 +343,12 @@ __global__ __launch_bounds__(64, 1) void k_rhs_march3d(const double *__restrict_
 }  // namespace dg
 
 // FP64 on uniform 3D grids at k = 1 and 2 without gravity, states below 4 GB
-// (32-bit byte offsets).  At k = 2 a grid of at most one 64-cell block per
-// compute unit stays on the MFMA kernel, whose 16-cell waves finish sooner
-// when the chip is not full (us per launch, MFMA against this kernel: 16^3 27.8,
-// 39.1; 25 x 25 x 26 36.5, 43; 26^3 55.2, 43.6; 32^3 57.4, 48.2; 64 x 9 x 100
-// 101, 61).
+// (32-bit byte offsets), of the sizes where it is faster.
 bool dg::march3d_takes(const dg_ctx *c) {
   if (c->sh.d != 3 || c->sh.k > 2 || c->amr || c->gravity || c->tree) return false;
   if (c->cfg.precision != DG_FP64 || c->cfg.path3d != DG_PATH3D_AUTO) return false;
   if (c->ncell * 8 * c->sh.nv * c->sh.N >= (1LL << 32)) return false;
-  return c->sh.k == 1 || c->ncell > 64 * 256;
+  return march3d_faster(c->sh.k, c->nx, c->ny, c->nz);
 }
 
 int dg::launch_march3d(const dg_ctx *c, const double *w, double *out, const double *dt, int mode, const Mix &mx,
@@ -369,7 +366,7 @@ int dg::launch_march3d(const dg_ctx *c, const double *w, double *out, const doub
   g.fac = 2.0 / c->dx / 8.0;
   g.gamma = c->cfg.gamma;
   const long row = (long)(g.nx + 2) * g.ny;
-  g.len = march_len(row, g.nz, c->sh.k == 1 ? 2048 : 1024);
+  g.len = march_len(row, g.nz, march_slots(c->sh.k));
   g.columns = row * ((g.nz + g.len - 1) / g.len);
   const dim3 nb((unsigned)((g.columns + 61) / 62));
   auto go = [&](auto K_, auto FX_) {

@@ -1,6 +1,7 @@
 // 3D right-hand side + stage, the work of 63 cells split over four waves
 // (FP64; uniform grids and the refined box).
 #include "dg_march.h"
+#include "dg_rules.h"
 
 namespace dg {
 
@@ -305,8 +306,9 @@ __device__ __forceinline__ void pick(int i, F &&f) {
 // axis: with three copies of it and the box's faces in the same kernel the
 // code outgrew the 64 KB instruction cache that two compute units share
 // (64^3 box at k = 3: 2310 us a stage, 1150 misses per cache).
-// Planes go to the workgroups in equal contiguous runs; a run or a column that
-// starts without a plane below it solves that z face first (pass 0).
+// Planes go to the workgroups, one per compute unit (150 KB of LDS), in equal
+// contiguous runs; a run or a column that starts without a plane below it
+// solves that z face first (pass 0).
 // Box: the coarse and the fine block are two such grids in one launch.  A fine
 // cell's coarse neighbour's trace is restricted to its quarter of the face; a
 // coarse cell's faces with the fine block get a zero flux here and theirs from
@@ -318,8 +320,6 @@ __device__ __forceinline__ void pick(int i, F &&f) {
 // 128^3 8581 -> 5149; a box of twice as many cells as its base grid, k = 3,
 // 64^3 2469 -> 1440 (both kernels), 24^3 163 -> 146, k = 2, 96 x 96 x 64 2178 ->
 // 1517, 32^3 145 -> 138, 8^3 58 -> 44.
-constexpr long kGroups = 256;  // workgroups of a launch: one per compute unit (150 KB of LDS)
-
 template <int K, int FX, bool AMR>
 __global__ __launch_bounds__(256, 1) void k_rhs_split3d(const double *__restrict__ w, double *__restrict__ out,
                                                         const double *__restrict__ dtp, Split3Grid g, int mode, Mix mx,
@@ -750,21 +750,18 @@ __global__ __launch_bounds__(64, 1) void k_box_faces(const double *__restrict__ 
 
 }  // namespace dg
 
-// FP64 in 3D without gravity, states below 4 GB (32-bit byte offsets): the
-// refined box at k = 2, 3, and uniform grids at k = 3 (k = 2 has the march and
-// MFMA kernels; here 16^3 takes 30.2 us against MFMA's 27.7, 25 x 25 x 26 57.8
-// against 37.0).  A grid whose cells fill the chip at most once on the MFMA
-// kernel (16-cell waves, four per SIMD) while its rows are too narrow for one
-// plane per workgroup here stays there (3 x 64 x 64: 91 us against 101; 24^3,
-// one plane each, 96 against 60).
+// FP64 in 3D without gravity, states below 4 GB (32-bit byte offsets), of the
+// sizes where it is faster: the refined box at k = 2, 3, and uniform grids at
+// k = 3 (k = 2 has the march and MFMA kernels; here 16^3 takes 30.2 us against
+// MFMA's 27.7, 25 x 25 x 26 57.8 against 37.0).
 bool dg::split3d_takes(const dg_ctx *c) {
   if (c->sh.d != 3 || c->sh.k < 2 || c->gravity || c->tree) return false;
   if (c->cfg.precision != DG_FP64 || c->cfg.path3d != DG_PATH3D_AUTO) return false;
   const long cells = c->amr ? c->ncc + c->ncf : c->ncell;
   if (cells * 8 * c->sh.nv * c->sh.N >= (1LL << 32)) return false;
-  if (c->amr) return true;
-  const long planes = ((c->nx + 1) * c->ny + 62) / 63 * c->nz;
-  return c->sh.k == 3 && !(planes > dg::kGroups && cells <= 64 * dg::kGroups);
+  const long n[3] = {c->nx, c->ny, c->nz};
+  if (c->amr) return split3d_box_faster(c->sh.k, n, c->nf);
+  return c->sh.k == 3 && split3d_faster(n[0], n[1], n[2]);
 }
 
 int dg::launch_split3d(const dg_ctx *c, const double *w, double *out, const double *dt, int mode, const Mix &mx,
@@ -784,12 +781,12 @@ int dg::launch_split3d(const dg_ctx *c, const double *w, double *out, const doub
     p.nc = i == 0 ? (long)n[0] * n[1] * n[2] : c->amr ? c->ncf : 0;
     p.base = i == 0 ? 0 : g.p[0].nc * c->sh.nv * c->sh.N;
     p.columns = (long)(p.n[0] + 1) * p.n[1];
-    p.planes = i == 0 || c->amr ? (p.columns + 62) / 63 * p.n[2] : 0;
+    p.planes = i == 0 || c->amr ? split_planes(p.n[0], p.n[1], p.n[2]) : 0;
     g.total += p.planes;
   }
   g.doubles = (g.p[0].nc + g.p[1].nc) * c->sh.nv * c->sh.N;
   g.gamma = c->cfg.gamma;
-  const dim3 nb((unsigned)std::min(kGroups, g.total));
+  const dim3 nb((unsigned)std::min(kCusPerGpu, g.total));
   auto go = [&](auto K_, auto FX_) {
     constexpr int K = decltype(K_)::value, FX = decltype(FX_)::value;
     if (c->amr) {
