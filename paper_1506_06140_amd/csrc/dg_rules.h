@@ -1,4 +1,5 @@
-// Which FP64 stage kernel a 3D grid runs on, from its sizes alone (host only).
+// Which FP64 kernel a stage runs on, from the grid's sizes alone (host only):
+// 3D stages and the 2D adjoint.
 #pragma once
 
 namespace dg {
@@ -78,6 +79,15 @@ inline bool split3d_box_faster(int k, const long n[3], const long nf[3]) {
   const long r = rounds(rounds(n[0] * n[1] * n[2], 64) + rounds(nf[0] * nf[1] * nf[2], 64), kCusPerGpu);
   const bool thin = nf[0] < 16;
   return k == 2 ? 30 + 20 * run <= 47 + 25 * r + (thin ? 20 : 0) : 42 + 41 * run <= 45 + 70 * r + (thin ? 30 : 0);
+}
+
+// k_adjoint_split2d against k_adjoint_quad2d (four lanes per cell): the former's
+// rows of nx + 1 positions are half idle at nx = 1, which at k = 3 costs more
+// than the split gains from three workgroups a compute unit on (us a stage, quad
+// against split: 1 x 8192 31, 21; 1 x 24000 41, 38; 1 x 32768 42, 53; 1 x 524288
+// 613, 765; 2 x 65536 145, 130; k = 2, 1 x 524288 397, 359).
+inline bool adjoint_split_faster(int k, long nx, long ny) {
+  return k < 3 || nx > 1 || rounds((nx + 1) * ny, 63) <= 3 * kCusPerGpu;
 }
 
 }  // namespace dg

@@ -1,4 +1,4 @@
-"""GPU: 3D FP64 stages on both sides of the choice between the sum-factorised
+"""GPU: FP64 stages on both sides of the choice between the sum-factorised
 kernels and the others, against the FP64 oracle: grids and boxes that are
 narrow in x or in x and y (one thread per cell, MFMA), and ones with several
 planes a workgroup of the four-wave kernel together with walls and both
@@ -72,3 +72,22 @@ def test_boxes(k, n, box, factorised, over, tmp_path):
     V, S, A = o.terms_cells(w, with_abs=True)
     check_rhs(o, s.rhs(_dev(w)).cpu().numpy(), V, S, A, f"{n} {box} rhs")
     _stages(s, o, w, u, f"{n} {box}")
+
+
+@pytest.mark.parametrize("ny,flux,bc", [(24192, 0, 0), (24193, 1, 0), (24500, 0, 1)])
+def test_adjoint_of_one_cell_rows(ny, flux, bc):
+    """Both sides of the 2D adjoint's choice at k = 3 (768 workgroups of 63
+    positions, two a cell): <mu, v> against the oracle's <lam, J v> to 1e-12 of
+    sum |lam_i (J v)_i|."""
+    import paper_1506_06140_amd as dg
+    from test_gpu_adjoint import _dev as dev, _state as state, _wl
+    print("route adjoint", ny, flux, bc, flush=True)
+    wl = _wl(dict(dim=2, k=3, n=(1, ny, 1), flux=flux, bc=(bc, bc, 0)))
+    o = oracle.Oracle(wl)
+    s = dg.Solver(wl)
+    rng = np.random.default_rng(7)
+    w, lam, v = state(o, 5), rng.normal(size=o.shape), rng.normal(size=o.shape)
+    mu = s.adjoint_rhs(dev(w), dev(lam)).cpu().numpy()
+    _, jv = o.jvp_rhs(w, v)
+    assert abs((mu * v).sum() - (lam * jv).sum()) <= 1e-12 * np.abs(lam * jv).sum()
+    assert s.status() == 0

@@ -1,6 +1,6 @@
-"""CPU: the choice between the 3D FP64 stage kernels, compiled for the host and
+"""CPU: the choice between the FP64 stage kernels, compiled for the host and
 checked against launches timed on both kernels (us: the one it may replace, the
-sum-factorised one), a tenth of slack for the two shapes it gets wrong."""
+sum-factorised one), a tenth of slack for shapes where the two are close."""
 import os
 import subprocess
 
@@ -15,7 +15,8 @@ int main() {
   int k, box;
   long n[6];
   while (scanf("%d %d %ld %ld %ld %ld %ld %ld", &k, &box, n, n + 1, n + 2, n + 3, n + 4, n + 5) == 8)
-    printf("%d\\n", box     ? (int)dg::split3d_box_faster(k, n, n + 3)
+    printf("%d\\n", box == 2 ? (int)dg::adjoint_split_faster(k, n[0], n[1])
+                   : box   ? (int)dg::split3d_box_faster(k, n, n + 3)
                    : k < 3 ? (int)dg::march3d_faster(k, n[0], n[1], n[2])
                            : (int)dg::split3d_faster(n[0], n[1], n[2]));
 }
@@ -48,6 +49,11 @@ TIMED = [
     (3, (20, 20, 20), ((5, 5, 5), (15, 15, 15)), 111.9, 128.2), (3, (3, 34, 34), ((1, 1, 1), (2, 33, 33)), 148.0, 138.4),
     (3, (48, 8, 32), ((8, 1, 4), (35, 4, 10)), 98.9, 143.7), (3, (28, 28, 28), ((7, 7, 7), (21, 21, 21)), 230.1, 183.7),
     (3, (64, 64, 64), ((16, 16, 16), (48, 48, 48)), 2469.0, 1440.0),
+    # 2D adjoint: four lanes per cell against the split over four waves
+    (1, (1, 524288, 1), "adjoint", 229.1, 186.4), (2, (1, 524288, 1), "adjoint", 396.7, 359.2),
+    (3, (1, 8192, 1), "adjoint", 30.8, 21.4), (3, (1, 24000, 1), "adjoint", 41.1, 37.8),
+    (3, (1, 32768, 1), "adjoint", 41.7, 52.7), (3, (1, 524288, 1), "adjoint", 613.2, 765.4),
+    (3, (2, 65536, 1), "adjoint", 145.2, 130.0), (3, (512, 512, 1), "adjoint", 320.0, 248.0),
 ]
 
 
@@ -58,8 +64,8 @@ def choices(work, cases):
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, "-o", exe, str(work / "rules.cpp")], check=True)
     rows = []
     for k, n, box, *_ in cases:
-        nf = [2 * (h - l) for l, h in zip(*box)] if box else [0, 0, 0]
-        rows.append(" ".join(str(x) for x in (k, int(box is not None), *n, *nf)))
+        nf = [2 * (h - l) for l, h in zip(*box)] if box and box != "adjoint" else [0, 0, 0]
+        rows.append(" ".join(str(x) for x in (k, 2 if box == "adjoint" else int(box is not None), *n, *nf)))
     out = subprocess.run([exe], input="\n".join(rows), capture_output=True, text=True, check=True).stdout.split()
     return [bool(int(x)) for x in out]
 
@@ -69,7 +75,7 @@ def chosen(tmp_path_factory):
     return choices(tmp_path_factory.mktemp("rules"), TIMED)
 
 
-@pytest.mark.parametrize("i", range(len(TIMED)), ids=["k%d_%s%s" % (t[0], "x".join(map(str, t[1])), "_box" if t[2] else "")
+@pytest.mark.parametrize("i", range(len(TIMED)), ids=["k%d_%s%s" % (t[0], "x".join(map(str, t[1])), "_adjoint" if t[2] == "adjoint" else "_box" if t[2] else "")
                                                       for t in TIMED])
 def test_the_faster_kernel_is_chosen(chosen, i):
     other, factorised = TIMED[i][3:]
