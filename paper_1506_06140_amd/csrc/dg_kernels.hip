@@ -3918,15 +3918,19 @@ struct LimitLaunch {
       if (c->amr) {
         // the fine block first: its boundary cells read whole coarse polynomials
         const long part[2][2] = {{c->ncc, c->ncf}, {0, c->ncc}};
+        constexpr long most = dg::launch_items(64 * (D + 2));
         for (const auto &pt : part) {
           if (chr)
             hipLaunchKernelGGL((dg::k_limit_amr<D, K>), dim3(nblocks(pt[1])), dim3(kBlock), 0, s, w,
                                make_amr_grid(c), pt[0], pt[1], c->cfg.beta, c->cfg.m_tilde, posit, c->cfg.eps, c->flag,
                                c->plist);
           else
-            hipLaunchKernelGGL((dg::k_limit_comp<D, K, true>), dim3((unsigned)((pt[1] + 63) / 64)),
-                               dim3(64 * (D + 2)), 0, s, w, dg::Grid{}, make_amr_grid(c), pt[0], pt[1], slope,
-                               c->cfg.beta, c->cfg.m_tilde, posit, c->cfg.eps, c->flag, c->plist);
+            for (long t = 0; t < pt[1]; t += most) {
+              const long n = std::min(most, pt[1] - t);
+              hipLaunchKernelGGL((dg::k_limit_comp<D, K, true>), dim3((unsigned)((n + 63) / 64)),
+                                 dim3(64 * (D + 2)), 0, s, w, dg::Grid{}, make_amr_grid(c), pt[0] + t, n, slope,
+                                 c->cfg.beta, c->cfg.m_tilde, posit, c->cfg.eps, c->flag, c->plist);
+            }
           HIP_TRY(hipGetLastError());
         }
         if (posit)

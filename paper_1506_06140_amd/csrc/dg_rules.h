@@ -1,8 +1,13 @@
-// Which FP64 kernel a stage runs on, from the grid's sizes alone (host only):
-// 3D stages and the 2D adjoint.
+// Rules on sizes alone (host only): how many items a launch takes, and which
+// FP64 kernel 3D stages and the 2D adjoint run on.
 #pragma once
 
 namespace dg {
+
+// Items that one launch may take of a kernel whose workgroups of `threads` take
+// 64 each: a launch holds fewer than 2^32 threads along a dimension, which
+// workgroups of several threads an item reach before the grids' 2^31 cells do.
+constexpr long launch_items(long threads) { return ((1L << 32) - 1) / threads * 64; }
 
 constexpr long kCusPerGpu = 256;            // MI355X
 constexpr long kSimdsPerGpu = 4 * kCusPerGpu;

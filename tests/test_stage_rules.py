@@ -75,6 +75,18 @@ def chosen(tmp_path_factory):
     return choices(tmp_path_factory.mktemp("rules"), TIMED)
 
 
+def test_a_launch_holds_less_than_2_to_the_32_threads(tmp_path):
+    (tmp_path / "items.cpp").write_text("""
+#include "dg_rules.h"
+constexpr bool fits(long threads) {
+  const long n = dg::launch_items(threads);
+  return n % 64 == 0 && n / 64 * threads < (1L << 32) && (n / 64 + 1) * threads >= (1L << 32);
+}
+static_assert(fits(256) && fits(320), "the most whole workgroups below 2^32 threads");
+""")
+    subprocess.run(["g++", "-std=c++17", "-fsyntax-only", "-I", CSRC, str(tmp_path / "items.cpp")], check=True)
+
+
 @pytest.mark.parametrize("i", range(len(TIMED)), ids=["k%d_%s%s" % (t[0], "x".join(map(str, t[1])), "_adjoint" if t[2] == "adjoint" else "_box" if t[2] else "")
                                                       for t in TIMED])
 def test_the_faster_kernel_is_chosen(chosen, i):
