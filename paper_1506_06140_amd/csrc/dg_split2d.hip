@@ -1,5 +1,8 @@
 // 2D right-hand side + stage, a cell's work split over four waves (FP64).
 #include "dg_march.h"
+#include "dg_rules.h"
+
+#include <algorithm>
 
 namespace dg {
 
@@ -374,7 +377,8 @@ template <int K, int FX, class Buf>
 __global__ __launch_bounds__(320, K <= 2 ? 3 : 2) void k_rhs_split_tree(const double *__restrict__ w,
                                                                        double *__restrict__ out,
                                                                        const double *__restrict__ dtp, TreeGrid g,
-                                                                       int mode, Mix mx, int *__restrict__ flag) {
+                                                                       long first, int mode, Mix mx,
+                                                                       int *__restrict__ flag) {
   constexpr int N = (K + 1) * (K + 2) / 2, n1 = K + 1;
   constexpr Line<K> L{};
   __shared__ double sv[4 * N * 64];       // volume term [v][l][lane]
@@ -384,8 +388,8 @@ __global__ __launch_bounds__(320, K <= 2 ? 3 : 2) void k_rhs_split_tree(const do
   const int nb = gridDim.x, xcd = blockIdx.x % 8, jb = blockIdx.x / 8;
   const long blk = (long)xcd * (nb / 8) + min(xcd, nb % 8) + jb;
   const long nl = g.nleaf;
-  const bool own = 64 * blk + lane < nl;
-  const unsigned leaf = (unsigned)min(64 * blk + lane, nl - 1);
+  const bool own = first + 64 * blk + lane < nl;
+  const unsigned leaf = (unsigned)min(first + 64 * blk + lane, nl - 1);
   using Off = typename Buf::Off;
   const Off cell = (Off)8 * leaf;
   const Buf ws(w, nl, 4 * N), os(out, nl, 4 * N);
@@ -417,8 +421,11 @@ __global__ __launch_bounds__(320, K <= 2 ? 3 : 2) void k_rhs_split_tree(const do
     const int side = role - 1;
     const int inf = g.info[(long)side * nl + leaf];
     const int kind = inf & 3, sub = (inf >> 2) & 1;
-    const unsigned j0 = kind == 1 ? leaf : (unsigned)g.nb[(long)(2 * side) * nl + leaf];
-    const unsigned j1 = kind == 2 ? (unsigned)g.nb[(long)(2 * side + 1) * nl + leaf] : leaf;
+    // both table entries are read whatever the kind (-1 where there is no
+    // neighbour): loads in a branch here had the compiler spill a register of
+    // all lanes inside it (K = 3, 64-bit form: wrong fluxes)
+    const int n0 = g.nb[(long)(2 * side) * nl + leaf], nh = g.nb[(long)(2 * side + 1) * nl + leaf];
+    const unsigned j0 = kind == 1 ? leaf : (unsigned)n0, j1 = kind == 2 ? (unsigned)nh : leaf;
     double co[4][n1], m[4][n1];
     auto face = [&](auto A_, auto S_) __attribute__((always_inline)) {
       constexpr int A = decltype(A_)::value, S = decltype(S_)::value;
@@ -596,7 +603,6 @@ int dg::launch_split2d(const dg_ctx *c, const double *w, double *out, const doub
 
 int dg::launch_split_tree(const dg_ctx *c, const TreeGrid &g, const double *w, double *out, const double *dt, int mode,
                           const Mix &mx, hipStream_t s) {
-  const dim3 nb((unsigned)((g.nleaf + 63) / 64));
   auto go = [&](auto K_) {
     constexpr int K = decltype(K_)::value;
     // 32-bit byte offsets up to 4 GB, else 64-bit ones
@@ -604,7 +610,10 @@ int dg::launch_split_tree(const dg_ctx *c, const TreeGrid &g, const double *w, d
     const bool dav = c->cfg.flux == DG_HLLC_DAVIS;
     auto kernel = dav ? (big ? k_rhs_split_tree<K, DG_HLLC_DAVIS, StatePtr> : k_rhs_split_tree<K, DG_HLLC_DAVIS, StateBuf>)
                       : (big ? k_rhs_split_tree<K, DG_HLLC_BATTEN, StatePtr> : k_rhs_split_tree<K, DG_HLLC_BATTEN, StateBuf>);
-    hipLaunchKernelGGL(kernel, nb, dim3(320), 0, s, w, out, dt, g, mode, mx, c->flag);
+    constexpr long most = launch_items(320);
+    for (long first = 0; first < g.nleaf; first += most)
+      hipLaunchKernelGGL(kernel, dim3((unsigned)((std::min(most, g.nleaf - first) + 63) / 64)), dim3(320), 0, s, w, out, dt,
+                         g, first, mode, mx, c->flag);
   };
   if (c->sh.k == 1) go(std::integral_constant<int, 1>{});
   else if (c->sh.k == 2) go(std::integral_constant<int, 2>{});
