@@ -61,6 +61,7 @@ __global__ __launch_bounds__(256, 2) void k_adjoint_split2d(
     int *__restrict__ flag) {
   constexpr int N = (K + 1) * (K + 2) / 2, NM = K * (K + 1) / 2, n1 = K + 1;
   constexpr Line<K> L{};
+  using Cell = typename Buf::Cell;
   using Off = typename Buf::Off;
   __shared__ double sv[4 * N * 64];           // [v][l][lane]: the cell's weights, then its volume term
   __shared__ double sd[4 * 2 * NM * 64];      // [v][axis][j][lane]: d(lam)/d xi_a
@@ -73,8 +74,8 @@ __global__ __launch_bounds__(256, 2) void k_adjoint_split2d(
   const int px = (int)(e % (g.nx + 1)), iy = (int)(e / (g.nx + 1));
   const bool own = px < g.nx && lane < 63 && e0 < g.columns;
   const Buf ws(w, g.nc, 4 * N), ls(lam, g.nc, 4 * N);
-  const Off nx8 = (Off)8 * (Off)g.nx, row = (Off)iy * nx8;
-  const Off cell = row + (Off)8 * (Off)(px < g.nx ? px : 0);
+  const Cell nx8 = (Cell)8 * (Cell)g.nx, row = (Cell)iy * nx8;
+  const Cell cell = row + (Cell)8 * (Cell)(px < g.nx ? px : 0);
 
   if (role == 0) {
 #pragma unroll
@@ -164,17 +165,17 @@ __global__ __launch_bounds__(256, 2) void k_adjoint_split2d(
 #pragma unroll
       for (int l = 0; l < N; ++l) sv[(v * N + l) * 64 + lane] = mu[v][l];
   } else {
-    Off lo = cell, hi = cell;
+    Cell lo = cell, hi = cell;
     bool gl = false, gh = false;  // ghost of a transmissive wall: the other side's trace, no equation
     if (role == 1) {
-      lo = row + (Off)8 * (Off)(px > 0 ? px - 1 : g.nx - 1);
+      lo = row + (Cell)8 * (Cell)(px > 0 ? px - 1 : g.nx - 1);
       gl = g.wall[0] && px == 0;
       gh = g.wall[0] && px == g.nx;
     } else if (role == 2) {
-      lo = iy > 0 ? cell - nx8 : cell + (Off)(g.ny - 1) * nx8;
+      lo = iy > 0 ? cell - nx8 : cell + (Cell)(g.ny - 1) * nx8;
       gl = g.wall[1] && iy == 0;
     } else {
-      hi = iy < g.ny - 1 ? cell + nx8 : cell - (Off)(g.ny - 1) * nx8;
+      hi = iy < g.ny - 1 ? cell + nx8 : cell - (Cell)(g.ny - 1) * nx8;
       gh = g.wall[1] && iy == g.ny - 1;
     }
     // the traces' coefficients in registers, the cotangent's in this wave's
@@ -324,15 +325,23 @@ int dg::launch_adjoint2d(const dg_ctx *c, const double *w, const double *lam, co
   const dim3 nb((unsigned)((g.columns + 62) / 63));
   auto go = [&](auto K_) {
     constexpr int K = decltype(K_)::value;
-    // 32-bit byte offsets up to 4 GB, else 64-bit ones
-    const bool big = c->ncell * 8LL * c->sh.nv * c->sh.N >= (1LL << 32);
-    const bool dav = c->cfg.flux == DG_HLLC_DAVIS;
-    auto kernel = dav ? (big ? k_adjoint_split2d<K, DG_HLLC_DAVIS, StatePtr> : k_adjoint_split2d<K, DG_HLLC_DAVIS, StateBuf>)
-                      : (big ? k_adjoint_split2d<K, DG_HLLC_BATTEN, StatePtr> : k_adjoint_split2d<K, DG_HLLC_BATTEN, StateBuf>);
+    // byte offsets of 32 bits in the state (below 4 GB), else in each plane
+    // (below 2^29 cells), else of 64 bits (from k = 2 on three such states do
+    // not fit the card)
+    auto pick = [&](auto B_) {
+      using Buf = std::remove_pointer_t<decltype(B_)>;
+      return c->cfg.flux == DG_HLLC_DAVIS ? k_adjoint_split2d<K, DG_HLLC_DAVIS, Buf> : k_adjoint_split2d<K, DG_HLLC_BATTEN, Buf>;
+    };
+    auto kernel = pick((StateBuf *)nullptr);
+    if (c->ncell * 8LL * c->sh.nv * c->sh.N >= (1LL << 32)) kernel = pick((StatePlanes *)nullptr);
+    if (c->ncell >= (1L << 29)) {
+      if constexpr (K > 1) return (int)hipErrorOutOfMemory;
+      else kernel = pick((StatePtr *)nullptr);
+    }
     hipLaunchKernelGGL(kernel, nb, dim3(256), 0, s, w, lam, acc, out, acc_out, dt, g, mode, ca, cb, c->flag);
+    return (int)hipGetLastError();
   };
-  if (c->sh.k == 1) go(std::integral_constant<int, 1>{});
-  else if (c->sh.k == 2) go(std::integral_constant<int, 2>{});
-  else go(std::integral_constant<int, 3>{});
-  return (int)hipGetLastError();
+  if (c->sh.k == 1) return go(std::integral_constant<int, 1>{});
+  if (c->sh.k == 2) return go(std::integral_constant<int, 2>{});
+  return go(std::integral_constant<int, 3>{});
 }

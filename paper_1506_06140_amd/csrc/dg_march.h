@@ -14,6 +14,7 @@ namespace dg {
 // state is below 4 GB), the (variable, mode) plane as the scalar offset, so a
 // load takes one vector register of address and no scalar base of its own.
 struct StateBuf {
+  using Cell = unsigned;
   using Off = unsigned;
   __amdgpu_buffer_rsrc_t r;
   unsigned plane;  // bytes of one (variable, mode) plane
@@ -33,8 +34,33 @@ struct StateBuf {
     __builtin_amdgcn_raw_buffer_store_b64(x, r, cell8, off, AUX);
   }
 };
-// A state of any size: 64-bit byte offsets.
+// A state whose planes are below 4 GB each: every plane a buffer of its own
+// (scalar arithmetic), the cell its 32-bit byte offset.
+struct StatePlanes {
+  using Cell = unsigned;
+  using Off = size_t;
+  double *p;
+  Off plane;
+  __device__ __forceinline__ StatePlanes(const double *q, long nc, int) : p(const_cast<double *>(q)), plane((Off)nc * 8) {}
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t at(Off off) const {
+    return __builtin_amdgcn_make_buffer_rsrc((char *)p + off, 0, (int)(unsigned)plane, 0x00027000);
+  }
+  template <int AUX = 0>
+  __device__ __forceinline__ double load(Cell cell8, Off off) const {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const u2 x = __builtin_amdgcn_raw_buffer_load_b64(at(off), cell8, 0, AUX);
+    return __hiloint2double((int)x.y, (int)x.x);
+  }
+  template <int AUX = 0>
+  __device__ __forceinline__ void store(double v, Cell cell8, Off off) const {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const u2 x = {(unsigned)__double2loint(v), (unsigned)__double2hiint(v)};
+    __builtin_amdgcn_raw_buffer_store_b64(x, at(off), cell8, 0, AUX);
+  }
+};
+// A state of any size: 64-bit byte offsets in vector registers.
 struct StatePtr {
+  using Cell = size_t;
   using Off = size_t;
   double *p;
   Off plane;
@@ -52,7 +78,7 @@ constexpr int NT = 2;  // non-temporal: data this launch touches once
 
 // the N weights of V variables of one cell, raw (off: byte offset of the first plane)
 template <int V, int N, int AUX = 0, class Buf>
-__device__ __forceinline__ void load_cell(const Buf &w, typename Buf::Off cell8, double (&r)[V][N],
+__device__ __forceinline__ void load_cell(const Buf &w, typename Buf::Cell cell8, double (&r)[V][N],
                                           typename Buf::Off off = 0) {
 #pragma unroll
   for (int v = 0; v < V; ++v)

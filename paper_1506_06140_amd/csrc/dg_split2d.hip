@@ -390,8 +390,9 @@ __global__ __launch_bounds__(320, K <= 2 ? 3 : 2) void k_rhs_split_tree(const do
   const long nl = g.nleaf;
   const bool own = first + 64 * blk + lane < nl;
   const unsigned leaf = (unsigned)min(first + 64 * blk + lane, nl - 1);
+  using Cell = typename Buf::Cell;
   using Off = typename Buf::Off;
-  const Off cell = (Off)8 * leaf;
+  const Cell cell = (Cell)8 * leaf;
   const Buf ws(w, nl, 4 * N), os(out, nl, 4 * N);
   if (threadIdx.x < 3 * n1 * n1) {
     const Line<K> &T = line_const<K>();
@@ -430,7 +431,7 @@ __global__ __launch_bounds__(320, K <= 2 ? 3 : 2) void k_rhs_split_tree(const do
     auto face = [&](auto A_, auto S_) __attribute__((always_inline)) {
       constexpr int A = decltype(A_)::value, S = decltype(S_)::value;
       double cn[4][n1];
-      auto traces = [&](auto T_, Off at, double (&c)[4][n1]) __attribute__((always_inline)) {
+      auto traces = [&](auto T_, Cell at, double (&c)[4][n1]) __attribute__((always_inline)) {
         constexpr int T = decltype(T_)::value;
 #pragma unroll
         for (int v0 = 0; v0 < 4; v0 += 2) {
@@ -441,7 +442,7 @@ __global__ __launch_bounds__(320, K <= 2 ? 3 : 2) void k_rhs_split_tree(const do
         }
       };
       traces(S_, cell, co);
-      traces(std::integral_constant<int, 1 - S>{}, (Off)8 * j0, cn);
+      traces(std::integral_constant<int, 1 - S>{}, (Cell)8 * j0, cn);
 #pragma unroll
       for (int v = 0; v < 4; ++v)
 #pragma unroll
@@ -450,7 +451,7 @@ __global__ __launch_bounds__(320, K <= 2 ? 3 : 2) void k_rhs_split_tree(const do
       for (int sb = 0; sb < 2; ++sb) {
         if (sb == 1) {
           if (!__any(kind == 2)) break;
-          traces(std::integral_constant<int, 1 - S>{}, (Off)8 * j1, cn);
+          traces(std::integral_constant<int, 1 - S>{}, (Cell)8 * j1, cn);
         }
         const double *to = st + (kind == 2 ? (1 + sb) * n1 * n1 : 0), *tn = st + (kind == 3 ? (1 + sub) * n1 * n1 : 0);
         const double half = kind == 2 ? 0.5 : (sb == 0 ? 1.0 : 0.0);
@@ -605,18 +606,26 @@ int dg::launch_split_tree(const dg_ctx *c, const TreeGrid &g, const double *w, d
                           const Mix &mx, hipStream_t s) {
   auto go = [&](auto K_) {
     constexpr int K = decltype(K_)::value;
-    // 32-bit byte offsets up to 4 GB, else 64-bit ones
-    const bool big = (long long)g.nleaf * 8 * c->sh.nv * c->sh.N >= (1LL << 32);
-    const bool dav = c->cfg.flux == DG_HLLC_DAVIS;
-    auto kernel = dav ? (big ? k_rhs_split_tree<K, DG_HLLC_DAVIS, StatePtr> : k_rhs_split_tree<K, DG_HLLC_DAVIS, StateBuf>)
-                      : (big ? k_rhs_split_tree<K, DG_HLLC_BATTEN, StatePtr> : k_rhs_split_tree<K, DG_HLLC_BATTEN, StateBuf>);
+    // byte offsets of 32 bits in the state (below 4 GB), else in each plane
+    // (below 2^29 leaves), else of 64 bits (at k = 3 a state and its stage would
+    // not fit the card)
+    auto pick = [&](auto B_) {
+      using Buf = std::remove_pointer_t<decltype(B_)>;
+      return c->cfg.flux == DG_HLLC_DAVIS ? k_rhs_split_tree<K, DG_HLLC_DAVIS, Buf> : k_rhs_split_tree<K, DG_HLLC_BATTEN, Buf>;
+    };
+    auto kernel = pick((StateBuf *)nullptr);
+    if ((long long)g.nleaf * 8 * c->sh.nv * c->sh.N >= (1LL << 32)) kernel = pick((StatePlanes *)nullptr);
+    if (g.nleaf >= (1L << 29)) {
+      if constexpr (K == 3) return (int)hipErrorOutOfMemory;
+      else kernel = pick((StatePtr *)nullptr);
+    }
     constexpr long most = launch_items(320);
     for (long first = 0; first < g.nleaf; first += most)
       hipLaunchKernelGGL(kernel, dim3((unsigned)((std::min(most, g.nleaf - first) + 63) / 64)), dim3(320), 0, s, w, out, dt,
                          g, first, mode, mx, c->flag);
+    return (int)hipGetLastError();
   };
-  if (c->sh.k == 1) go(std::integral_constant<int, 1>{});
-  else if (c->sh.k == 2) go(std::integral_constant<int, 2>{});
-  else go(std::integral_constant<int, 3>{});
-  return (int)hipGetLastError();
+  if (c->sh.k == 1) return go(std::integral_constant<int, 1>{});
+  if (c->sh.k == 2) return go(std::integral_constant<int, 2>{});
+  return go(std::integral_constant<int, 3>{});
 }
