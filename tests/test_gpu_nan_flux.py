@@ -1,5 +1,5 @@
-"""GPU: a cell whose trace has no real sound speed (negative pressure) makes
-every flux through its faces NaN, whichever side of the face it is on and
+"""GPU: a cell whose trace has no real sound speed (negative pressure, or an
+infinite energy, density or momentum) makes every flux through its faces NaN, whichever side of the face it is on and
 however the flow runs, the mass flux too, and raises the context's flag: the
 density's tendency is NaN in that cell and in its face neighbours (of the
 refined box and the quadtree also across a level) and finite elsewhere."""
@@ -15,24 +15,28 @@ CASES = [(2, 1, (64, 5, 1)), (2, 2, (33, 17, 1)), (2, 3, (63, 4, 1)), (2, 4, (17
          (3, 1, (62, 5, 7)), (3, 2, (26, 26, 25)), (3, 3, (64, 3, 4))]
 
 
-def _spoil(w, dim, cell):
-    """Negative pressure in one cell: its energy below its kinetic energy."""
+def _spoil(w, dim, cell, how="pressure"):
+    """One bad cell: its energy below its kinetic energy, or an infinite mean."""
+    if how != "pressure":
+        w[({"density": 0, "momentum": 2, "energy": dim + 1}[how], 0) + cell] = np.inf
+        return
     w[(dim + 1, 0) + cell] = 0.25 * sum(w[(1 + a, 0) + cell] ** 2 for a in range(dim)) / w[(0, 0) + cell]
 
 
 @pytest.mark.parametrize("flux", [0, 1])
 @pytest.mark.parametrize("sign", [1.0, -1.0])
+@pytest.mark.parametrize("how", ["pressure", "density", "momentum", "energy"])
 @pytest.mark.parametrize("dim,k,n", CASES)
-def test_bad_trace_spoils_every_flux(dim, k, n, sign, flux):
+def test_bad_trace_spoils_every_flux(dim, k, n, how, sign, flux):
     import torch
     import paper_1506_06140_amd as dg
-    print("nan flux", dim, k, n, sign, flux, flush=True)
+    print("nan flux", dim, k, n, how, sign, flux, flush=True)
     wl = workloads.workload("kh3d" if dim == 3 else "density_wave", dim=dim, k=k, n=n, flux=flux, limiter=0,
                             positivity=0, rk="rk3", length=tuple(m / 64 for m in n))
     s = dg.Solver(wl)
     w = supersonic(s.shape, dim, sign, 7)
     at = (n[2] // 2, n[1] // 2, 3)
-    _spoil(w, dim, at)
+    _spoil(w, dim, at, how)
     want = np.zeros(s.shape[2:], dtype=bool)
     want[at] = True
     for a in range(dim):
