@@ -1,6 +1,12 @@
 // HIP kernels of libdg for CDNA4 (gfx950) and the C ABI declared in dg.h.
 //
-// Work decomposition: one thread per cell.  A thread
+// FP64 stages and the 2D adjoint run on the sum-factorised kernels of
+// dg_split2d.hip, dg_march3d.hip, dg_split3d.hip and dg_adjoint2d.hip where their
+// rules take the grid (dg_line.hip, dg_rules.h).  Here are the stage kernels of
+// the other grids and precisions (2D tiles, 3D contractions on MFMA, one thread
+// or four lanes per cell), the limiters, the time step, the meshes' changes and
+// the 3D adjoint.  In the plainest stage kernel (k_rhs_stage, one thread per
+// cell) a thread
 //   1. reads the cell's modal weights (coalesced: x-fastest SoA layout),
 //   2. evaluates the volume integral of eq. dg_term2: the state at each
 //      (k+1)^d Gauss node, the Euler flux there, and the projection onto

@@ -22,9 +22,8 @@ struct MarchGrid {
 // the cell, so its moments are 2^3 times the momentum's own weights (the rule
 // integrates their products exactly).
 // The result starts from the lower z face's moments m and goes to set(v, row).
-template <int K, class W, class Get, class Set>
-__device__ __forceinline__ void volume_term(W &&w, double gm1, const double (&m)[5][(K + 1) * (K + 2) / 2], Get &&,
-                                            Set &&set) {
+template <int K, class W, class Set>
+__device__ __forceinline__ void volume_term(W &&w, double gm1, const double (&m)[5][(K + 1) * (K + 2) / 2], Set &&set) {
   constexpr int n1 = K + 1, N = (K + 1) * (K + 2) * (K + 3) / 6, N2 = (K + 1) * (K + 2) / 2;
   constexpr int NM = K * (K + 1) * (K + 2) / 6;
   constexpr Line<K> L{};
@@ -64,7 +63,7 @@ __device__ __forceinline__ void volume_term(W &&w, double gm1, const double (&m)
           double t = c2[v][mode_index<2>(ex, 0, 0)];
           static_for<1, n1 - ex>([&](auto G_) {
             constexpr int ey = decltype(G_)::value;
-            if constexpr (true) t = L.p[iy][ey] == 0.0 ? t : fma(c2[v][mode_index<2>(ex, ey, 0)], L.p[iy][ey], t);
+            t = L.p[iy][ey] == 0.0 ? t : fma(c2[v][mode_index<2>(ex, ey, 0)], L.p[iy][ey], t);
           });
           c1[ex] = t;
         });
@@ -256,7 +255,7 @@ __global__ __launch_bounds__(64, 1) void k_rhs_march3d(const double *__restrict_
       }
     }
     if (s == g.len) break;
-    volume_term<K>([&](int v, int l) __attribute__((always_inline)) { return wc[v][l]; }, gm1, m, acc_row, set_acc);
+    volume_term<K>([&](int v, int l) __attribute__((always_inline)) { return wc[v][l]; }, gm1, m, set_acc);
     DG_FENCE;
     // x faces: each lane the face to the lane below it
 #pragma unroll

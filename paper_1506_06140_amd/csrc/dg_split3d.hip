@@ -595,49 +595,47 @@ __global__ __launch_bounds__(256, 1) void k_rhs_split3d(const double *__restrict
         });
         __syncthreads();
       }
-      if (last) {
-        const bool hole = AMR && !fine && in_hole(cx, iy, z);
-        unsigned st = stride;
-        asm volatile("" : "+s"(st));
-        const unsigned off0 = (unsigned)(role * NO) * st;
-        double u[NO], y0[NO];
-        {
-          unsigned off = off0;
+      const bool hole = AMR && !fine && in_hole(cx, iy, z);
+      unsigned st = stride;
+      asm volatile("" : "+s"(st));
+      const unsigned off0 = (unsigned)(role * NO) * st;
+      double u[NO], y0[NO];
+      {
+        unsigned off = off0;
 #pragma unroll
-          for (int i = 0; i < NO; ++i) {  // (past the last plane: the buffer's bound gives 0)
-            u[i] = ws.load(cell, off);
-            y0[i] = ys.load<NT>(cell, off);
-            off += st;
-          }
+        for (int i = 0; i < NO; ++i) {  // (past the last plane: the buffer's bound gives 0)
+          u[i] = ws.load(cell, off);
+          y0[i] = ys.load<NT>(cell, off);
+          off += st;
         }
-        const double cl = hole ? 0.0 : cldt, a0 = mx.a[0];
+      }
+      const double cl = hole ? 0.0 : cldt, a0 = mx.a[0];
 #pragma unroll
-        for (int i = 0; i < NO; ++i) {
-          const int c = role * NO + i;
-          const double L = hole ? 0.0 : P.fac * sa[(5 * N % 4 == 0 ? c : min(c, 5 * N - 1)) * 64 + lane];
-          bad |= own && L != L;
-          const double o = fma(cl, L, cu * u[i]), o1 = fma(a0, y0[i], o);  // mix_out
-          u[i] = mode == 0 ? L : ny0 > 0 ? o1 : o;
-        }
+      for (int i = 0; i < NO; ++i) {
+        const int c = role * NO + i;
+        const double L = hole ? 0.0 : P.fac * sa[(5 * N % 4 == 0 ? c : min(c, 5 * N - 1)) * 64 + lane];
+        bad |= own && L != L;
+        const double o = fma(cl, L, cu * u[i]), o1 = fma(a0, y0[i], o);  // mix_out
+        u[i] = mode == 0 ? L : ny0 > 0 ? o1 : o;
+      }
 #pragma unroll 1
-        for (int k = 1; k < ny0; ++k) {
-          const StateBuf yk(mx.y[k], g.doubles, 1);
-          unsigned off = off0;
-#pragma unroll
-          for (int i = 0; i < NO; ++i) {
-            u[i] = fma(mx.a[k], yk.load<NT>(cell, off), u[i]);
-            off += st;
-          }
-        }
+      for (int k = 1; k < ny0; ++k) {
+        const StateBuf yk(mx.y[k], g.doubles, 1);
         unsigned off = off0;
 #pragma unroll
         for (int i = 0; i < NO; ++i) {
-          if (own && (5 * N % 4 == 0 || role * NO + i < 5 * N)) os.store<NT>(u[i], cell, off);
+          u[i] = fma(mx.a[k], yk.load<NT>(cell, off), u[i]);
           off += st;
         }
-        __syncthreads();
-        if (role == 3) start();
       }
+      unsigned off = off0;
+#pragma unroll
+      for (int i = 0; i < NO; ++i) {
+        if (own && (5 * N % 4 == 0 || role * NO + i < 5 * N)) os.store<NT>(u[i], cell, off);
+        off += st;
+      }
+      __syncthreads();
+      if (role == 3) start();
     }
   }
   if (bad) atomicOr(flag, FLAG_NAN);
