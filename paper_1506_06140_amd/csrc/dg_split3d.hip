@@ -598,21 +598,29 @@ __global__ __launch_bounds__(256, 1) void k_rhs_split3d(const double *__restrict
       const bool hole = AMR && !fine && in_hole(cx, iy, z);
       unsigned st = stride;
       asm volatile("" : "+s"(st));
-      const unsigned off0 = (unsigned)(role * NO) * st;
+      // this wave's NO rows of the 5 N; past the last one the last again, not
+      // stored (no read may lie outside the state: a row's offset is the buffer
+      // instruction's scalar one, which may be larger than what follows a small
+      // fine block)
+      const int row0 = role * NO;
+      const unsigned off0 = (unsigned)row0 * st;
+      auto next = [&](unsigned off, int i) __attribute__((always_inline)) {
+        return 5 * N % 4 == 0 || row0 + i + 1 < 5 * N ? off + st : off;
+      };
       double u[NO], y0[NO];
       {
         unsigned off = off0;
 #pragma unroll
-        for (int i = 0; i < NO; ++i) {  // (past the last plane: the buffer's bound gives 0)
+        for (int i = 0; i < NO; ++i) {
           u[i] = ws.load(cell, off);
           y0[i] = ys.load<NT>(cell, off);
-          off += st;
+          off = next(off, i);
         }
       }
       const double cl = hole ? 0.0 : cldt, a0 = mx.a[0];
 #pragma unroll
       for (int i = 0; i < NO; ++i) {
-        const int c = role * NO + i;
+        const int c = row0 + i;
         const double L = hole ? 0.0 : P.fac * sa[(5 * N % 4 == 0 ? c : min(c, 5 * N - 1)) * 64 + lane];
         bad |= own && L != L;
         const double o = fma(cl, L, cu * u[i]), o1 = fma(a0, y0[i], o);  // mix_out
@@ -625,14 +633,14 @@ __global__ __launch_bounds__(256, 1) void k_rhs_split3d(const double *__restrict
 #pragma unroll
         for (int i = 0; i < NO; ++i) {
           u[i] = fma(mx.a[k], yk.load<NT>(cell, off), u[i]);
-          off += st;
+          off = next(off, i);
         }
       }
       unsigned off = off0;
 #pragma unroll
       for (int i = 0; i < NO; ++i) {
-        if (own && (5 * N % 4 == 0 || role * NO + i < 5 * N)) os.store<NT>(u[i], cell, off);
-        off += st;
+        if (own && (5 * N % 4 == 0 || row0 + i < 5 * N)) os.store<NT>(u[i], cell, off);
+        off = next(off, i);
       }
       __syncthreads();
       if (role == 3) start();

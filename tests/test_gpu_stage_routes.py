@@ -27,6 +27,7 @@ BOXES = [
     (2, (3, 3, 300), ((1, 1, 1), (2, 2, 299)), False, dict(bc=(1, 1, 1))),
     (3, (3, 3, 300), ((1, 1, 1), (2, 2, 299)), False, dict(flux=1)),
     (2, (12, 12, 40), ((1, 1, 1), (11, 11, 39)), True, dict(bc=(1, 1, 1))),
+    (2, (16, 16, 16), ((7, 7, 7), (8, 8, 8)), True, dict(flux=1)),  # a fine block of a few cells at the state's end
     (3, (8, 8, 40), ((1, 1, 1), (7, 7, 39)), True, dict(bc=(0, 1, 1), flux=1)),
 ]
 
