@@ -52,7 +52,7 @@ __device__ __forceinline__ void edge_coefs_t(const double (&m)[K + 1], double (&
 // 15 cycles of the load unit each) and the FP64 rate (four sweeps of 320
 // operations) in about equal parts, behind them HBM (420 MB at 512^2, 80 us).
 // A stage, four lanes per cell with every face swept from both sides before:
-// k = 3, 32^2 29.0 -> 14.6, 256^2 80 -> 60, 512^2 320 -> 248 us; k = 2, 256^2
+// k = 3, 32^2 29.0 -> 14.2, 256^2 80 -> 58, 512^2 320 -> 241 us; k = 2, 256^2
 // 59 -> 31; k = 1, 64^2 12.1 -> 8.4, 512^2 135 -> 59.
 template <int K, int FX, class Buf>
 __global__ __launch_bounds__(256, 2) void k_adjoint_split2d(

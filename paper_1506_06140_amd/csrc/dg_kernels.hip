@@ -3018,7 +3018,8 @@ __global__ __launch_bounds__(256, 2) void k_limit_amr(double *__restrict__ w, Am
 // means for either side): 64^3 box k = 3 225 -> 140 us (a blast's, with a
 // third of the cells limited, 250 -> 147 without k_positivity), 16^3 68 -> 16;
 // 96 x 96 x 64 box k = 2 314 -> 161, k = 1 129 -> 84; 256^2 box k = 3 40 -> 17;
-// uniform 128^3 k = 2 218 -> 194, 32^3 9.0 -> 7.9.  On the other uniform grids
+// uniform 128^3 k = 2, by what is limited: a shear layer 258 -> 217, a shock tube
+// 251 -> 228, a wave (nothing) 160 -> 175; 32^3 9.0 -> 7.9.  On the other uniform grids
 // one thread per cell stays (2D k = 3 512^2 18.0 against 19.8 here; 3D k = 1
 // 128^3 70, 96; k = 3 100^3 137, 168): there its loads were in flight together
 // already and this form's many short waves cost more than its parallelism.
