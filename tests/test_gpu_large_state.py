@@ -165,6 +165,29 @@ def test_adjoint_above_4_gb(k, n, tiles):
     assert s.status() == 0
 
 
+def test_adjoint_above_2_to_the_29_cells():
+    """Planes of 4 GB and more: 64-bit lane addresses (k = 1; three states of 52 GB)."""
+    import torch
+    import paper_1506_06140_amd as dg
+    print("adjoint above 2^29 cells", flush=True)
+    _room(170)
+    n, tiles = (50, 37, 1), (464, 626, 1)
+    over = dict(dim=2, k=1, limiter=0, positivity=0, rk="rk3")
+    small = dg.Solver(workloads.workload("density_wave", n=n, length=tuple(m / 64 for m in n), **over))
+    big = tuple(m * t for m, t in zip(n, tiles))
+    s = dg.Solver(workloads.workload("density_wave", n=big, length=tuple(m / 64 for m in big), **over))
+    assert s.ncell >= 2 ** 29
+    shape = (4, s.N, 1, n[1], n[0])
+    w, lam = _state(shape, 2, 1), np.random.default_rng(3).normal(size=shape)
+    mu = small.adjoint_rhs(_dev(w).view(small.shape), _dev(lam).view(small.shape)).cpu().numpy().reshape(shape)
+    wd, ld = _tiled(s, w, tiles), _tiled(s, lam, tiles)
+    out = s.adjoint_rhs(wd, ld)
+    assert np.abs(_worst(out, mu, tiles) - mu).max() <= 1e-12 * np.abs(mu).max()
+    assert s.status() == 0
+    del wd, ld, out, s
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("k,n,flux", [(1, (14, 12), 0), (2, (14, 12), 1), (3, (14, 12), 0)])
 def test_tree_stage_above_4_gb(k, n, flux):
     import torch
